@@ -67,6 +67,7 @@ constexpr int kExactCap = 64;
 constexpr int kMaxShift = 54;  // kFine << kMaxShift covers all 64-bit distances
 constexpr int kRegK = kInlineSurvivors;  // survivors kept in registers
 constexpr int kRegCand = 1;              // extension candidates kept in registers per thread
+constexpr int kFlooredFrom = 4;          // candidates per thread from which a frame gets a score floor
 constexpr int kChunk = 32;               // frame headers staged per chunk
 constexpr int kWaypoints = 256;
 constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull;
@@ -637,11 +638,11 @@ __device__ __forceinline__ int32_t surv_by_rank(const FrameCtx<MB>& f, int k, do
 }
 
 // Extension of entry i (seen as `v`) by non-blank survivor k: distance of its score below
-// the reference, or ~0 when it has no mass or coincides with a beam entry.
+// the reference, or ~0 when it has no mass, lies below `floor` or coincides with a beam entry.
 template <int LM, int MB>
 __device__ __forceinline__ uint64_t eval_ext_of(const FrameCtx<MB>& f, const EntryView& v, int i,
                                                 int k, const uint32_t* kidset, int kid_slots,
-                                                int32_t& tok) {
+                                                double floor, int32_t& tok) {
     double lps;
     const int32_t s = surv_by_rank(f, f.nb0 + k, lps);
     tok = s;
@@ -650,7 +651,7 @@ __device__ __forceinline__ uint64_t eval_ext_of(const FrameCtx<MB>& f, const Ent
     }
     const double src = (s == v.last) ? v.pb : v.ptot;
     const double sc = src + lps + lm_term<LM>(f, v.last, s);
-    if (!(sc > -INFINITY)) return kAllOnes;
+    if (!(sc > -INFINITY) || sc < floor) return kAllOnes;
     return f.Rk - order_key(sc);
 }
 
@@ -867,7 +868,8 @@ __device__ __forceinline__ void emit_ext_prefetched(const FrameCtx<MB>& f, BeamS
 // asks for (no spills: the fastest single workgroup); 3 and 4 spill a few registers (each
 // frame some per cent slower) so that more utterances are resident when the batch has more
 // workgroups than the chip can hold at 2.
-template <int LM, int THREADS, int MB, int WAVES>
+// FLOOR: built with the score floor for long survivor lists (see `floored`).
+template <int LM, int THREADS, int MB, int WAVES, bool FLOOR>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 void beam_kernel(BeamArgs a) {
     constexpr int kThreads = THREADS;
@@ -879,6 +881,7 @@ void beam_kernel(BeamArgs a) {
     static_assert(THREADS >= MB, "one thread per beam entry");
     // builds with 512 threads or more take a thread's candidates from one entry (see EntryView)
     constexpr bool kEntryMajor = THREADS >= kThreadsLarge;
+    static_assert(kEntryMajor || !FLOOR, "the floor is made for the entry-major mapping");
     static_assert(kEntryMajor || !kColdGlobal, "the largest capacity has no children lists");
     // Builds with four wavefronts read what a staying entry carries over together with its
     // masses (measured: cfg 3 -1.7%); the larger builds, shorter of registers, read it when the
@@ -901,6 +904,10 @@ void beam_kernel(BeamArgs a) {
     __shared__ FrameHdr ring[kChunk];
     __shared__ uint64_t sh_selD, sh_selH, sh_kbest;
     __shared__ uint64_t sh_minD;  // smallest distance (= best score) among a frame's candidates
+    // frames with a score floor (see `floored`)
+    __shared__ uint64_t sh_floor;  // complement of the largest of the entries' own distances
+    __shared__ int32_t sh_toptok;  // non-blank token with the frame's top emission, if there is one
+    __shared__ int32_t sh_below;   // candidates below the floor
     __shared__ int32_t sh_nnew, sh_blcount, sh_best;
     __shared__ unsigned long long sh_stat[8];
     __shared__ __align__(16) int32_t newslot[kMaxBeam];  // old beam index -> new beam index of an entry that stays
@@ -976,6 +983,11 @@ void beam_kernel(BeamArgs a) {
         sh_nnew = 0;
         sh_blcount = 0;
         sh_minD = kAllOnes;
+        if (FLOOR) {
+            sh_floor = kAllOnes;
+            sh_toptok = INT32_MAX;
+            sh_below = 0;
+        }
     }
     if (tid < 8) sh_stat[tid] = 0ull;
     if (carried) {  // the beam as the previous chunk left it
@@ -1179,7 +1191,10 @@ void beam_kernel(BeamArgs a) {
             for (int k = tid; k < K; k += kThreads) {
                 const Survivor s = (k < kRegK) ? full->first[k] : recs[k];
                 s_tok[k] = (uint16_t)s.tok;
-                if (kEntryMajor) s_lp[k] = s.lp;
+                if (kEntryMajor) {
+                    s_lp[k] = s.lp;
+                    if (FLOOR && s.lp == hd.top && s.tok != 0) atomicMin(&sh_toptok, s.tok);
+                }
                 dense_lp[s.tok] = s.lp;
             }
         }
@@ -1207,6 +1222,22 @@ void beam_kernel(BeamArgs a) {
         const bool ext_thread = ext_g < G && ext_g < fc.Knb;  // kEntryMajor only
         const int M = kEntryMajor ? (fc.Knb + G - 1) / G  // most candidates any thread has
                                   : (n_ext + kThreads - 1) / kThreads;
+        // Frames with thousands of candidates: nearly all of them lie far below the beam's cut.
+        // With the beam full, every entry i stands for one candidate of its own, the better of
+        // "i stays" and "i extended by the frame's top token": that is `beam` different
+        // candidates, so whatever scores below the worst of these cannot be kept.  One barrier
+        // makes that floor known before the extensions are looked at; those below it are only
+        // counted, four at a time, and never reach the histogram, the distance cache or the
+        // probe of the pair table.  (128 utterances, V = 1024, every token kept, beam 64: 38.4 ms
+        // per decode without the floor, 11.3 ms with it.  A floor from a histogram of the same few
+        // candidates, whose resolution is a bin: 17.0 ms.)
+        const bool floored = FLOOR && big && M >= kFlooredFrom && n_live == beam;  // uniform
+        double floor = -INFINITY;
+        int n_below = 0;  // this thread's candidates below the floor
+        // groups of 2^gshift candidate numbers of which some lane's candidate is not below the
+        // floor (wave-uniform); the passes after the first one visit only these
+        uint64_t groups = kAllOnes;
+        const int gshift = M > 64 ? 26 - __builtin_clz((unsigned)(M - 1)) : 0;
         const uint32_t* const kids = kidset2[gen];
         EntryView ev;
         ev.last = -1;
@@ -1226,7 +1257,7 @@ void beam_kernel(BeamArgs a) {
         auto cand_eval = [&](int e, int k, int& se, int32_t& tk) -> uint64_t {
             if (kEntryMajor) {
                 se = ext_i;
-                return eval_ext_of<LM>(fc, ev, ext_i, k, kids, kKidSlots, tk);
+                return eval_ext_of<LM>(fc, ev, ext_i, k, kids, kKidSlots, floor, tk);
             }
             return eval_ext<LM>(fc, e, se, tk);
         };
@@ -1255,7 +1286,7 @@ void beam_kernel(BeamArgs a) {
         if constexpr (kEntryMajor) {
             if (ext_thread) {
                 ev = view_entry(fc, ext_i);
-                cD0 = cand_eval(0, ext_g, cI0, cT0);
+                if (!floored) cD0 = cand_eval(0, ext_g, cI0, cT0);
             }
         } else {
             if (e_first < n_ext)
@@ -1264,6 +1295,7 @@ void beam_kernel(BeamArgs a) {
         PHASE_MARK(8);
         // ... and the stay candidate of entry `tid`
         double my_pb = -INFINITY, my_pnb = -INFINITY, my_tot = -INFINITY;
+        double merged = -INFINITY;  // the parent's extension that merges into this entry
         uint64_t D_stay = kAllOnes;
         StayFields sf;
         sf.h = sf.hp = 0;
@@ -1290,10 +1322,44 @@ void beam_kernel(BeamArgs a) {
                 const double ptp = cur->ptot[p];
                 const double src = (lpar == lj && !collapsed) ? cur->pb[p] : ptp;
                 a2 = src + lpl + lm_term<LM>(fc, lpar, lj);
+                if (FLOOR) merged = a2;
             }
             my_pnb = lse2(a1, a2);
             my_tot = lse2(my_pb, my_pnb);
             if (my_tot > -INFINITY) D_stay = Rk - order_key(my_tot);
+        }
+        if constexpr (FLOOR) {
+            if (floored) {
+                uint64_t best_inv = kAllOnes;  // complement of the distance of the entry's own best
+                if (tid < n_live) {
+                    const int j = tid;
+                    double own = my_tot;
+                    const int32_t top_tok = sh_toptok;
+                    if (top_tok != INT32_MAX && !kidset_has(kids, kKidSlots, j, top_tok)) {
+                        const EntryView me = view_entry(fc, j);
+                        const double src = (top_tok == me.last) ? me.pb : me.ptot;
+                        const double sc = src + (double)hd.top + lm_term<LM>(fc, me.last, top_tok);
+                        own = sc > own ? sc : own;
+                    }
+                    best_inv = own > -INFINITY ? ~(Rk - order_key(own)) : 0;
+                }
+                const uint64_t wave_inv = wave_min_u64(best_inv);
+                if (lane == 0 && wave_inv != kAllOnes)
+                    atomicMin((unsigned long long*)&sh_floor, (unsigned long long)wave_inv);
+                lds_barrier();
+                const uint64_t worst = ~sh_floor;
+                floor = worst <= Rk ? key_value(Rk - worst) : -INFINITY;
+                // the pair behind a merge is no candidate, but is counted below like any other
+                if (merged > -INFINITY && merged < floor) n_below = -1;
+                if (ext_thread) {
+                    cT0 = ext_token(fc, ext_g);
+                    const double src = (cT0 == ev.last) ? ev.pb : ev.ptot;
+                    const double sc =
+                        src + (double)s_lp[fc.nb0 + ext_g] + lm_term<LM>(fc, ev.last, cT0);
+                    if (sc > -INFINITY && sc < floor) ++n_below;
+                    else cD0 = cand_eval(0, ext_g, cI0, cT0);
+                }
+            }
         }
         PHASE_MARK(1);
 
@@ -1339,10 +1405,70 @@ void beam_kernel(BeamArgs a) {
                 if (FLTOP_RARE(windowed)) {
                     nearest = D_stay < cD0 ? D_stay : cD0;
                 }
-                if (FLTOP_RARE(M > kRegCand)) {
+                if (FLOOR && kFirst && floored) {
+                    int n_clamp = 0;
+                    groups = 0;
+                    for (int m0 = kRegCand; m0 < M; m0 += 4) {
+                        // the four reads of each kind go out together
+                        int32_t tk4[4];
+                        double sc4[4];
+                        bool up4[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int k = fc.nb0 + ext_g + G * (m0 + u);
+                            up4[u] = ext_thread && k < K && m0 + u < M;
+                            const int at = up4[u] ? k : 0;
+                            tk4[u] = (int32_t)s_tok[at];
+                            sc4[u] = (double)s_lp[at];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const double src = (tk4[u] == ev.last) ? ev.pb : ev.ptot;
+                            sc4[u] = src + sc4[u] + lm_term<LM>(fc, ev.last, tk4[u]);
+                        }
+                        bool any_up = false;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const bool alive = up4[u] && sc4[u] > -INFINITY;
+                            up4[u] = alive && !(sc4[u] < floor);
+                            n_below += (alive && !up4[u]) ? 1 : 0;
+                            any_up |= up4[u];
+                        }
+                        uint64_t D4[4] = {kAllOnes, kAllOnes, kAllOnes, kAllOnes};
+                        if (__ballot(any_up) != 0) {  // rare in a long list
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                if (__ballot(up4[u]) == 0) continue;
+                                groups |= 1ull << ((m0 + u) >> gshift);
+                                if (up4[u] && !(((ev.kidmask >> (tk4[u] & 31)) & 1u) &&
+                                                kidset_has(kids, kKidSlots, ext_i, tk4[u]))) {
+                                    const uint64_t D = Rk - order_key(sc4[u]);
+                                    D4[u] = D;
+                                    if (windowed) nearest = D < nearest ? D : nearest;
+                                    hist_add_many(fc, w, D, ext_i, tk4[u], hfine, hcoarse, n_clamp);
+                                }
+                            }
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int row = m0 + u - kRegCand;
+                            if (row < drows) dcache[row * kThreads] = D4[u];
+                        }
+                    }
+                    const int wave_clamp = wave_inclusive_scan(n_clamp);  // lane 63: the sum
+                    const int wave_below = wave_inclusive_scan(n_below);
+                    if (lane == kWave - 1) {
+                        if (wave_clamp > 0) {
+                            atomicAdd(&hfine[kFine - 1], (uint32_t)wave_clamp);
+                            atomicAdd(&hcoarse[kCoarse - 1], (uint32_t)wave_clamp);
+                        }
+                        if (wave_below != 0) atomicAdd(&sh_below, wave_below);
+                    }
+                } else if (FLTOP_RARE(M > kRegCand)) {
                     int n_clamp = 0;
                     for (int m = kRegCand; m < M; ++m) {
                         int e, k;
+                        if (FLOOR && ((groups >> (m >> gshift)) & 1ull) == 0) continue;
                         if (!cand_at(m, e, k)) continue;  // (and none at any later m)
                         int se = 0;
                         int32_t tk = 0;
@@ -1397,8 +1523,9 @@ void beam_kernel(BeamArgs a) {
                 const int fine_row = (lane & 16) ? lstar : lmin;
                 const int fine_val = (int)hfine[fine_row * 16 + (lane & 15)];
                 if (kFirst) {
-                    pd_cand += (uint32_t)total;
-                    pd_peak = max(pd_peak, (uint32_t)total);
+                    const int below = FLOOR && floored ? sh_below : 0;
+                    pd_cand += (uint32_t)(total + below);
+                    pd_peak = max(pd_peak, (uint32_t)(total + below));
                     // first occupied bin -> bound of the best candidate (window starts at 0)
                     if (FLTOP_USUAL(occ != 0)) {
                         const uint32_t f = (uint32_t)fine_val;
@@ -1451,6 +1578,7 @@ void beam_kernel(BeamArgs a) {
                         boundary_add(fc, w, bstar, cD0, cI0, cT0, &sh_blcount, bl_D, bl_h);
                     for (int m = kRegCand; m < M; ++m) {
                         int e, k;
+                        if (FLOOR && ((groups >> (m >> gshift)) & 1ull) == 0) continue;
                         if (!cand_at(m, e, k)) continue;  // (and none at any later m)
                         int se = 0;
                         int32_t tk = 0;
@@ -1562,6 +1690,7 @@ void beam_kernel(BeamArgs a) {
             }
         }
         for (int m = kRegCand; m < M; ++m) {  // candidates beyond the register cache
+            if (FLOOR && ((groups >> (m >> gshift)) & 1ull) == 0) continue;
             int e, k;
             const bool there = cand_at(m, e, k);
             bool sel = false;
@@ -1705,6 +1834,11 @@ void beam_kernel(BeamArgs a) {
         }
         if (tid == 0) {
             sh_minD = kAllOnes;
+            if (FLOOR) {
+                sh_floor = kAllOnes;
+                sh_toptok = INT32_MAX;
+                sh_below = 0;
+            }
             if (a.frame_beam) a.frame_beam[trace_base + t] = n_new;
         }
         if (big)
@@ -2082,6 +2216,12 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // (large vocabulary: eight wavefronts per utterance while the whole batch is resident that
     // way, two workgroups per CU, four beyond: B = 1024, V = 1024: 143 M frames/s against
     // 120 M; B = 512: 93 M against 111 M)
+    // Builds with the score floor where a frame can reach kFlooredFrom candidates per thread at
+    // all (a full beam, every token kept); elsewhere the code for it only costs registers
+    // (measured: beam 1000 with the 4 best tokens 6% slower, V = 32 unpruned 4%).
+    const int per_entry = (huge_beam ? kThreadsHuge : kThreadsLarge) / p.beam;
+    const bool long_lists =
+        kept_at_most > kRegK && kept_at_most > (kFlooredFrom - 1) * (per_entry > 0 ? per_entry : 1);
     const bool tiny_state = p.beam <= kBeamTiny && carried == nullptr;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
@@ -2093,32 +2233,26 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
         a.dcache_rows = dense ? 1 : (wide ? 12 : 8);
         dyn += (size_t)a.dcache_rows * threads * sizeof(uint64_t);
     }
+#define FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, FLOOR_)                               \
+    hipLaunchKernelGGL((beam_kernel<LM_, THREADS_, MB_, WAVES_, FLOOR_>), dim3((unsigned)B), \
+                       dim3(THREADS_), dyn, stream, a)
+#define FLTOP_LAUNCH_EITHER(LM_, THREADS_, MB_, WAVES_)                      \
+    do {                                                                     \
+        if (long_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, true); \
+        else FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, false);          \
+    } while (0)
 #define FLTOP_LAUNCH_BEAM(LM_)                                                               \
     do {                                                                                     \
-        if (huge_beam)                                                                       \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsHuge, kBeamHuge, 4>),               \
-                               dim3((unsigned)B), dim3(kThreadsHuge), dyn, stream, a);       \
-        else if (large_beam)                                                                 \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsLarge, kBeamLarge, 2>),             \
-                               dim3((unsigned)B), dim3(kThreadsLarge), dyn, stream, a);      \
+        if (huge_beam) FLTOP_LAUNCH_EITHER(LM_, kThreadsHuge, kBeamHuge, 4);                 \
+        else if (large_beam) FLTOP_LAUNCH_EITHER(LM_, kThreadsLarge, kBeamLarge, 2);         \
         else if (wide && very_dense)                                                         \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsSmall, kBeamSmall, 4>),             \
-                               dim3((unsigned)B), dim3(kThreadsSmall), dyn, stream, a);      \
-        else if (wide && dense)                                                              \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsLarge, kBeamSmall, 4>),             \
-                               dim3((unsigned)B), dim3(kThreadsLarge), dyn, stream, a);      \
-        else if (wide)                                                                       \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsLarge, kBeamSmall, 2>),             \
-                               dim3((unsigned)B), dim3(kThreadsLarge), dyn, stream, a);      \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 4, false);                    \
+        else if (wide && dense) FLTOP_LAUNCH_EITHER(LM_, kThreadsLarge, kBeamSmall, 4);      \
+        else if (wide) FLTOP_LAUNCH_EITHER(LM_, kThreadsLarge, kBeamSmall, 2);               \
         else if (dense && tiny_state)                                                        \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsDense, kBeamTiny, 3>),              \
-                               dim3((unsigned)B), dim3(kThreadsDense), dyn, stream, a);      \
-        else if (dense)                                                                      \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsDense, kBeamSmall, 3>),             \
-                               dim3((unsigned)B), dim3(kThreadsDense), dyn, stream, a);      \
-        else                                                                                 \
-            hipLaunchKernelGGL((beam_kernel<LM_, kThreadsSmall, kBeamSmall, 2>),             \
-                               dim3((unsigned)B), dim3(kThreadsSmall), dyn, stream, a);      \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamTiny, 3, false);                     \
+        else if (dense) FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamSmall, 3, false);        \
+        else FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 2, false);                   \
     } while (0)
     if (p.lm_table == nullptr)
         FLTOP_LAUNCH_BEAM(kLmNone);
@@ -2127,6 +2261,8 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     else
         FLTOP_LAUNCH_BEAM(kLmGlobal);
 #undef FLTOP_LAUNCH_BEAM
+#undef FLTOP_LAUNCH_EITHER
+#undef FLTOP_LAUNCH_BUILD
     return hipGetLastError();
 }
 
