@@ -887,6 +887,15 @@ void beam_kernel(BeamArgs a) {
     // masses (measured: cfg 3 -1.7%); the larger builds, shorter of registers, read it when the
     // entry is copied (measured there: +0.4% to +1.4% otherwise).
     constexpr bool kPrefetchStay = !kEntryMajor;
+    // Where the last bin's count is handed over: inside the block of a thread's later candidates,
+    // which the usual frame of a pruned small vocabulary jumps over, or behind it.  A second
+    // branch there costs the 256- and 128-thread builds 2-3% (64 utterances x 500 frames, V = 32,
+    // beam 32: 625 against 644 us; 4096 of them: 2287 against 2327 us).  The 256-thread build for
+    // batches of large vocabularies beyond the chip, whose frames mostly have later candidates,
+    // is faster with it (600 utterances x 100 frames, V = 1024: 668 against 698 us; with a table in
+    // memory 748 against 740 us, so not there).
+    constexpr bool kClampApart =
+        kEntryMajor || (THREADS == kThreadsSmall && WAVES == 4 && LM != kLmGlobal);
     // Which way a uniform branch of the frame loop usually goes, for the block layout of the
     // four-wavefront builds: a lone wavefront per SIMD pays for every taken branch, and with the
     // usual path laid out straight a frame is 2-4% shorter (the set below was chosen by timing
@@ -1382,6 +1391,14 @@ void beam_kernel(BeamArgs a) {
             w.Dfix = 0;
             int need = beam;
             const bool windowed = a.beam_window > 0.0;  // uniform
+            // a wavefront's candidates in the last bin: one atomic per level
+            auto add_clamped = [&](int n_clamp) {
+                const int wave_clamp = wave_inclusive_scan(n_clamp);  // lane 63: the sum
+                if (lane == kWave - 1 && wave_clamp > 0) {
+                    atomicAdd(&hfine[kFine - 1], (uint32_t)wave_clamp);
+                    atomicAdd(&hcoarse[kCoarse - 1], (uint32_t)wave_clamp);
+                }
+            };
             // One pass over the candidates: histogram, scan, and either the threshold (true) or a
             // narrower window for the next pass (false).  The first pass, the only one in all but
             // a few frames, is compiled with its window constants folded in.
@@ -1487,13 +1504,10 @@ void beam_kernel(BeamArgs a) {
                         if (D != kAllOnes)
                             hist_add_many(fc, w, D, se, tk, hfine, hcoarse, n_clamp);
                     }
+                    if constexpr (!kClampApart) add_clamped(n_clamp);
                 }
-                if (kEntryMajor || M > kRegCand) {
-                    const int wave_clamp = wave_inclusive_scan(n_clamp);  // lane 63: the sum
-                    if (lane == kWave - 1 && wave_clamp > 0) {
-                        atomicAdd(&hfine[kFine - 1], (uint32_t)wave_clamp);
-                        atomicAdd(&hcoarse[kCoarse - 1], (uint32_t)wave_clamp);
-                    }
+                if constexpr (kClampApart) {
+                    if (kEntryMajor || M > kRegCand) add_clamped(n_clamp);
                 }
                 if (kFirst && windowed) {  // one LDS atomic per wavefront
                     const uint64_t wave_nearest = wave_min_u64(nearest);
