@@ -501,6 +501,11 @@ __device__ __forceinline__ double lp_of(const FrameCtx<MB>& f, int32_t tok) {
     return (double)pick_lp(tok, t0, t1, t2, t3, t4, t5, l0, l1, l2, l3, l4, l5);
 }
 
+// What the kernel is built for, as to the survivor lists of the frames it will meet (512 and
+// 1024 threads; see launch_beam): short ones, as a threshold leaves them, every token of a
+// vocabulary that gives a thread two or three candidates, or lists long enough for a score floor.
+enum : int { kListsShort = 0, kListsWhole = 1, kListsLong = 2 };
+
 // The LM flavour is a kernel template parameter: with one kernel serving all three, the
 // LDS read and the global read would meet at a joint wait on both memory counters.
 enum : int { kLmNone = 0, kLmLds = 1, kLmGlobal = 2 };
@@ -689,7 +694,7 @@ __device__ __forceinline__ void hist_add(const FrameCtx<MB>& f, const Window& w,
 }
 
 // The same for the candidates beyond the register cache, of which a frame may have
-// thousands.  All that lie beyond the window share the last bin, and one LDS word cannot
+// thousands (and for all of a thread's, see kCountAll).  All that lie beyond the window share the last bin, and one LDS word cannot
 // take that many atomics quickly: those are counted in a register (`n_clamp`) instead.
 template <int MB>
 __device__ __forceinline__ void hist_add_many(const FrameCtx<MB>& f, const Window& w, uint64_t D,
@@ -868,8 +873,8 @@ __device__ __forceinline__ void emit_ext_prefetched(const FrameCtx<MB>& f, BeamS
 // asks for (no spills: the fastest single workgroup); 3 and 4 spill a few registers (each
 // frame some per cent slower) so that more utterances are resident when the batch has more
 // workgroups than the chip can hold at 2.
-// FLOOR: built with the score floor for long survivor lists (see `floored`).
-template <int LM, int THREADS, int MB, int WAVES, bool FLOOR>
+// LISTS: the survivor lists it is made for (kListsShort for builds with 256 and 128 threads).
+template <int LM, int THREADS, int MB, int WAVES, int LISTS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 void beam_kernel(BeamArgs a) {
     constexpr int kThreads = THREADS;
@@ -881,12 +886,19 @@ void beam_kernel(BeamArgs a) {
     static_assert(THREADS >= MB, "one thread per beam entry");
     // builds with 512 threads or more take a thread's candidates from one entry (see EntryView)
     constexpr bool kEntryMajor = THREADS >= kThreadsLarge;
-    static_assert(kEntryMajor || !FLOOR, "the floor is made for the entry-major mapping");
+    static_assert(kEntryMajor || LISTS == kListsShort, "the others are made for the entry-major mapping");
+    constexpr bool FLOOR = LISTS == kListsLong;  // with the score floor (see `floored`)
     static_assert(kEntryMajor || !kColdGlobal, "the largest capacity has no children lists");
     // Builds with four wavefronts read what a staying entry carries over together with its
     // masses (measured: cfg 3 -1.7%); the larger builds, shorter of registers, read it when the
     // entry is copied (measured there: +0.4% to +1.4% otherwise).
     constexpr bool kPrefetchStay = !kEntryMajor;
+    // Whether a thread counts all its candidates of the last bin in a register, its stay and first
+    // extension included: hundreds of a frame's candidates may lie beyond the histogram's window,
+    // and atomics on one word queue up (64 utterances x 500 frames, V = 32, every token kept: 2354
+    // -> 2270 us).  Frames of short lists have few there and pay for the wavefront's sum (64 x 500
+    // frames, V = 32, beam 200, R = 0.1: 609 -> 623 us; V = 100, beam 8, table in memory: 605 -> 627).
+    constexpr bool kCountAll = LISTS != kListsShort;
     // Where the last bin's count is handed over: inside the block of a thread's later candidates,
     // which the usual frame of a pruned small vocabulary jumps over, or behind it.  A second
     // branch there costs the 256- and 128-thread builds 2-3% (64 utterances x 500 frames, V = 32,
@@ -895,7 +907,7 @@ void beam_kernel(BeamArgs a) {
     // is faster with it (600 utterances x 100 frames, V = 1024: 668 against 698 us; with a table in
     // memory 748 against 740 us, so not there).
     constexpr bool kClampApart =
-        kEntryMajor || (THREADS == kThreadsSmall && WAVES == 4 && LM != kLmGlobal);
+        kCountAll || (THREADS == kThreadsSmall && WAVES == 4 && LM != kLmGlobal);
     // Which way a uniform branch of the frame loop usually goes, for the block layout of the
     // four-wavefront builds: a lone wavefront per SIMD pays for every taken branch, and with the
     // usual path laid out straight a frame is 2-4% shorter (the set below was chosen by timing
@@ -1417,10 +1429,7 @@ void beam_kernel(BeamArgs a) {
                     lds_barrier();
                 }
                 int n_clamp = 0;  // this thread's candidates in the last bin
-                // (entry-major builds count all of theirs there in a register: hundreds of a
-                // frame's candidates lie beyond the window, and atomics on one word queue up;
-                // 64 utterances, V = 32, every token kept: 2.33 -> 2.20 ms)
-                if constexpr (kEntryMajor) {
+                if constexpr (kCountAll) {
                     if (D_stay != kAllOnes)
                         hist_add_many(fc, w, D_stay, tid, -1, hfine, hcoarse, n_clamp);
                     if (cD0 != kAllOnes)
@@ -1507,7 +1516,7 @@ void beam_kernel(BeamArgs a) {
                     if constexpr (!kClampApart) add_clamped(n_clamp);
                 }
                 if constexpr (kClampApart) {
-                    if (kEntryMajor || M > kRegCand) add_clamped(n_clamp);
+                    if (kCountAll || M > kRegCand) add_clamped(n_clamp);
                 }
                 if (kFirst && windowed) {  // one LDS atomic per wavefront
                     const uint64_t wave_nearest = wave_min_u64(nearest);
@@ -2240,6 +2249,10 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     const int per_entry = (huge_beam ? kThreadsHuge : kThreadsLarge) / p.beam;
     const bool long_lists =
         kept_at_most > kRegK && kept_at_most > (kFlooredFrom - 1) * (per_entry > 0 ? per_entry : 1);
+    // A search that keeps every token, but of a vocabulary that gives no thread that many: up to
+    // three candidates per thread, of which most lie beyond the histogram's window (see kCountAll;
+    // the 1024-thread build, which gets there with at most six tokens per frame, gains nothing).
+    const bool whole_lists = !long_lists && p.rel_threshold == 0.0f;
     const bool tiny_state = p.beam <= kBeamTiny && carried == nullptr;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
@@ -2251,26 +2264,31 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
         a.dcache_rows = dense ? 1 : (wide ? 12 : 8);
         dyn += (size_t)a.dcache_rows * threads * sizeof(uint64_t);
     }
-#define FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, FLOOR_)                               \
-    hipLaunchKernelGGL((beam_kernel<LM_, THREADS_, MB_, WAVES_, FLOOR_>), dim3((unsigned)B), \
+#define FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, LISTS_)                               \
+    hipLaunchKernelGGL((beam_kernel<LM_, THREADS_, MB_, WAVES_, LISTS_>), dim3((unsigned)B), \
                        dim3(THREADS_), dyn, stream, a)
-#define FLTOP_LAUNCH_EITHER(LM_, THREADS_, MB_, WAVES_)                      \
-    do {                                                                     \
-        if (long_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, true); \
-        else FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, false);          \
+#define FLTOP_LAUNCH_SHORT_OR_LONG(LM_, THREADS_, MB_, WAVES_)                        \
+    do {                                                                              \
+        if (long_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsLong);   \
+        else FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsShort);             \
+    } while (0)
+#define FLTOP_LAUNCH_ANY_LISTS(LM_, THREADS_, MB_, WAVES_)                            \
+    do {                                                                              \
+        if (whole_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsWhole); \
+        else FLTOP_LAUNCH_SHORT_OR_LONG(LM_, THREADS_, MB_, WAVES_);                  \
     } while (0)
 #define FLTOP_LAUNCH_BEAM(LM_)                                                               \
     do {                                                                                     \
-        if (huge_beam) FLTOP_LAUNCH_EITHER(LM_, kThreadsHuge, kBeamHuge, 4);                 \
-        else if (large_beam) FLTOP_LAUNCH_EITHER(LM_, kThreadsLarge, kBeamLarge, 2);         \
+        if (huge_beam) FLTOP_LAUNCH_SHORT_OR_LONG(LM_, kThreadsHuge, kBeamHuge, 4);          \
+        else if (large_beam) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamLarge, 2);      \
         else if (wide && very_dense)                                                         \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 4, false);                    \
-        else if (wide && dense) FLTOP_LAUNCH_EITHER(LM_, kThreadsLarge, kBeamSmall, 4);      \
-        else if (wide) FLTOP_LAUNCH_EITHER(LM_, kThreadsLarge, kBeamSmall, 2);               \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 4, kListsShort);              \
+        else if (wide && dense) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamSmall, 4);   \
+        else if (wide) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamSmall, 2);            \
         else if (dense && tiny_state)                                                        \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamTiny, 3, false);                     \
-        else if (dense) FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamSmall, 3, false);        \
-        else FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 2, false);                   \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamTiny, 3, kListsShort);               \
+        else if (dense) FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamSmall, 3, kListsShort);  \
+        else FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 2, kListsShort);             \
     } while (0)
     if (p.lm_table == nullptr)
         FLTOP_LAUNCH_BEAM(kLmNone);
@@ -2279,7 +2297,8 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     else
         FLTOP_LAUNCH_BEAM(kLmGlobal);
 #undef FLTOP_LAUNCH_BEAM
-#undef FLTOP_LAUNCH_EITHER
+#undef FLTOP_LAUNCH_ANY_LISTS
+#undef FLTOP_LAUNCH_SHORT_OR_LONG
 #undef FLTOP_LAUNCH_BUILD
     return hipGetLastError();
 }
