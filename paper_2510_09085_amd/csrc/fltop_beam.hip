@@ -1054,6 +1054,8 @@ void beam_kernel(BeamArgs a) {
     fc.lm_beta = a.lm_beta;
     fc.V = V;
 
+    // non-blank survivors up to which no thread has kFlooredFrom candidates (full beam)
+    const int floored_above = (kFlooredFrom - 1) * (kThreads / beam);
     int mapped_for = -1;  // kEntryMajor: the beam size the thread -> entry mapping was made for
     int ext_i = 0, ext_g = 0, ext_G = 1;
     int gen = 0;         // beam generation: slab[gen], links[gen]
@@ -1206,6 +1208,18 @@ void beam_kernel(BeamArgs a) {
             t = t_end;
             continue;
         }
+        const int nb0 = hd.first[0].tok == 0 ? 1 : 0;  // survivors ascend by token: the blank, if kept, is the first
+        // Frames with thousands of candidates: nearly all of them lie far below the beam's cut.
+        // With the beam full, every entry i stands for one candidate of its own, the better of
+        // "i stays" and "i extended by the frame's top token": that is `beam` different
+        // candidates, so whatever scores below the worst of these cannot be kept.  One barrier
+        // makes that floor known before the extensions are looked at; those below it are only
+        // counted, four at a time, and never reach the histogram or the probe of the pair table
+        // (in the distance cache they are marked as gone).  (128 utterances, V = 1024, every token
+        // kept, beam 64: 38.1 ms per decode without the floor, 11.3 ms with it.  A floor from a
+        // histogram of the same few candidates, whose resolution is a bin: 17.0 ms.)
+        const bool floored_frame =  // uniform
+            FLOOR && big && n_live == beam && K - nb0 > floored_above;
         if (big) {
             const Survivor* recs = rec_all + ((int64_t)hd.rec_base - kRegK);
             const FrameHdr* full = &ring[t % kChunk];
@@ -1214,7 +1228,7 @@ void beam_kernel(BeamArgs a) {
                 s_tok[k] = (uint16_t)s.tok;
                 if (kEntryMajor) {
                     s_lp[k] = s.lp;
-                    if (FLOOR && s.lp == hd.top && s.tok != 0) atomicMin(&sh_toptok, s.tok);
+                    if (floored_frame && s.lp == hd.top && s.tok != 0) atomicMin(&sh_toptok, s.tok);
                 }
                 dense_lp[s.tok] = s.lp;
             }
@@ -1222,7 +1236,7 @@ void beam_kernel(BeamArgs a) {
         if (big) lds_barrier();
 
         PHASE_MARK(0);
-        fc.nb0 = hd.first[0].tok == 0 ? 1 : 0;  // survivors ascend by token: the blank, if kept, is the first
+        fc.nb0 = nb0;
         fc.Knb = K - fc.nb0;
         fc.div_magic = hd.div_magic;
         const double lp_blank = fc.nb0 ? (double)hd.first[0].lp : -INFINITY;
@@ -1243,507 +1257,23 @@ void beam_kernel(BeamArgs a) {
         const bool ext_thread = ext_g < G && ext_g < fc.Knb;  // kEntryMajor only
         const int M = kEntryMajor ? (fc.Knb + G - 1) / G  // most candidates any thread has
                                   : (n_ext + kThreads - 1) / kThreads;
-        // Frames with thousands of candidates: nearly all of them lie far below the beam's cut.
-        // With the beam full, every entry i stands for one candidate of its own, the better of
-        // "i stays" and "i extended by the frame's top token": that is `beam` different
-        // candidates, so whatever scores below the worst of these cannot be kept.  One barrier
-        // makes that floor known before the extensions are looked at; those below it are only
-        // counted, four at a time, and never reach the histogram, the distance cache or the
-        // probe of the pair table.  (128 utterances, V = 1024, every token kept, beam 64: 38.4 ms
-        // per decode without the floor, 11.3 ms with it.  A floor from a histogram of the same few
-        // candidates, whose resolution is a bin: 17.0 ms.)
-        const bool floored = FLOOR && big && M >= kFlooredFrom && n_live == beam;  // uniform
-        double floor = -INFINITY;
-        int n_below = 0;  // this thread's candidates below the floor
-        // groups of 2^gshift candidate numbers of which some lane's candidate is not below the
-        // floor (wave-uniform); the passes after the first one visit only these
-        uint64_t groups = kAllOnes;
-        const int gshift = M > 64 ? 26 - __builtin_clz((unsigned)(M - 1)) : 0;
-        const uint32_t* const kids = kidset2[gen];
-        EntryView ev;
-        ev.last = -1;
-        ev.kidmask = 0u;
-        ev.ptot = ev.pb = -INFINITY;
-        // candidate number m of this thread: does it exist, and what names it
-        auto cand_at = [&](int m, int& e, int& k) -> bool {
-            if (kEntryMajor) {
-                k = ext_g + G * m;
-                e = 0;
-                return ext_thread && k < fc.Knb;
-            }
-            e = e_first + m * kThreads;
-            k = 0;
-            return e < n_ext;
-        };
-        auto cand_eval = [&](int e, int k, int& se, int32_t& tk) -> uint64_t {
-            if (kEntryMajor) {
-                se = ext_i;
-                return eval_ext_of<LM>(fc, ev, ext_i, k, kids, kKidSlots, floor, tk);
-            }
-            return eval_ext<LM>(fc, e, se, tk);
-        };
-        auto cand_name = [&](int e, int k, int& se, int32_t& tk) {  // without evaluating it
-            if (kEntryMajor) {
-                se = ext_i;
-                tk = ext_token(fc, k);
-            } else {
-                double lp_unused;
-                cand_of(fc, e, se, tk, lp_unused);
-            }
-        };
-
+        uint64_t selD = kAllOnes;  // with selH: keep D < selD or (D == selD and hash <= selH)
+        uint64_t kbest_key = 0;    // upper bound of the best candidate's key
         // upper bound of every candidate score -> reference key
         const double ref = kmax_v + (double)hd.top + lm_ub + 1.0986122886681098 + 1e-3;
         fc.Rk = order_key(ref);
         const uint64_t Rk = fc.Rk;
-
-        // ---- candidates owned by this thread ----------------------------------------
-        // the first extension candidate stays in registers (the others, if any, are worked
-        // on one after the other and leave their distances in LDS) ...
-        ExtSource xs0{};
-        uint64_t cD0 = kAllOnes;  // ~0 marks "no live candidate"
-        int cI0 = 0;
-        int32_t cT0 = 0;
-        if constexpr (kEntryMajor) {
-            if (ext_thread) {
-                ev = view_entry(fc, ext_i);
-                if (!floored) cD0 = cand_eval(0, ext_g, cI0, cT0);
+        if constexpr (FLOOR) {
+            if (floored_frame) {
+                constexpr bool floored = true;
+#include "fltop_beam_frame.inc"
+            } else {
+                constexpr bool floored = false;
+#include "fltop_beam_frame.inc"
             }
         } else {
-            if (e_first < n_ext)
-                cD0 = eval_ext<LM, MB, kPrefetchStay>(fc, e_first, cI0, cT0, &ccur, &xs0);
-        }
-        PHASE_MARK(8);
-        // ... and the stay candidate of entry `tid`
-        double my_pb = -INFINITY, my_pnb = -INFINITY, my_tot = -INFINITY;
-        double merged = -INFINITY;  // the parent's extension that merges into this entry
-        uint64_t D_stay = kAllOnes;
-        StayFields sf;
-        sf.h = sf.hp = 0;
-        sf.par = sf.last = sf.node = sf.plen = sf.xanc = -1;
-        if (tid < n_live) {
-            const int j = tid;
-            const int32_t lj = cur->last[j];
-            if constexpr (kPrefetchStay) {
-                sf.h = cur->h[j];
-                sf.hp = ccur.hp(j);
-                sf.node = ccur.node(j);
-                sf.plen = ccur.plen(j);
-                sf.xanc = ccur.xanc(j);
-                sf.last = lj;
-            }
-            const double lpl = lp_of(fc, lj);
-            my_pb = cur->ptot[j] + lp_blank;
-            const double a1 = (collapsed ? -INFINITY : cur->pnb[j]) + lpl;
-            double a2 = -INFINITY;
-            const int p = lk->par[j];
-            if constexpr (kPrefetchStay) sf.par = p;
-            if (p >= 0 && lpl > -INFINITY) {
-                const int32_t lpar = cur->last[p];
-                const double ptp = cur->ptot[p];
-                const double src = (lpar == lj && !collapsed) ? cur->pb[p] : ptp;
-                a2 = src + lpl + lm_term<LM>(fc, lpar, lj);
-                if (FLOOR) merged = a2;
-            }
-            my_pnb = lse2(a1, a2);
-            my_tot = lse2(my_pb, my_pnb);
-            if (my_tot > -INFINITY) D_stay = Rk - order_key(my_tot);
-        }
-        if constexpr (FLOOR) {
-            if (floored) {
-                uint64_t best_inv = kAllOnes;  // complement of the distance of the entry's own best
-                if (tid < n_live) {
-                    const int j = tid;
-                    double own = my_tot;
-                    const int32_t top_tok = sh_toptok;
-                    if (top_tok != INT32_MAX && !kidset_has(kids, kKidSlots, j, top_tok)) {
-                        const EntryView me = view_entry(fc, j);
-                        const double src = (top_tok == me.last) ? me.pb : me.ptot;
-                        const double sc = src + (double)hd.top + lm_term<LM>(fc, me.last, top_tok);
-                        own = sc > own ? sc : own;
-                    }
-                    best_inv = own > -INFINITY ? ~(Rk - order_key(own)) : 0;
-                }
-                const uint64_t wave_inv = wave_min_u64(best_inv);
-                if (lane == 0 && wave_inv != kAllOnes)
-                    atomicMin((unsigned long long*)&sh_floor, (unsigned long long)wave_inv);
-                lds_barrier();
-                const uint64_t worst = ~sh_floor;
-                floor = worst <= Rk ? key_value(Rk - worst) : -INFINITY;
-                // the pair behind a merge is no candidate, but is counted below like any other
-                if (merged > -INFINITY && merged < floor) n_below = -1;
-                if (ext_thread) {
-                    cT0 = ext_token(fc, ext_g);
-                    const double src = (cT0 == ev.last) ? ev.pb : ev.ptot;
-                    const double sc =
-                        src + (double)s_lp[fc.nb0 + ext_g] + lm_term<LM>(fc, ev.last, cT0);
-                    if (sc > -INFINITY && sc < floor) ++n_below;
-                    else cD0 = cand_eval(0, ext_g, cI0, cT0);
-                }
-            }
-        }
-        PHASE_MARK(1);
-
-        // ---- selection: find (selD, selH); keep D < selD or (D == selD and hash <= selH)
-        uint64_t selD = kAllOnes, selH = kAllOnes;
-        uint64_t kbest_key = 0;  // upper bound of the best candidate's key
-        uint64_t Dcut = kAllOnes;  // candidates farther than this from the reference lie
-                                   // outside the score window
-        {
-            // initial bucket width from the spread of the current beam
-            const double est_low = kmin_v + (double)hd.top - 2.0;
-            uint64_t Dest = Rk - order_key(est_low);
-            if (Dest < 1024) Dest = 1024;
-            Window w;
-            w.sh = 64 - __clzll((long long)Dest) - 10;
-            if (w.sh < 0) w.sh = 0;
-            if (w.sh > kMaxShift) w.sh = kMaxShift;
-            w.lo = 0;
-            w.mode = 0;
-            w.Dfix = 0;
-            int need = beam;
-            const bool windowed = a.beam_window > 0.0;  // uniform
-            // a wavefront's candidates in the last bin: one atomic per level
-            auto add_clamped = [&](int n_clamp) {
-                const int wave_clamp = wave_inclusive_scan(n_clamp);  // lane 63: the sum
-                if (lane == kWave - 1 && wave_clamp > 0) {
-                    atomicAdd(&hfine[kFine - 1], (uint32_t)wave_clamp);
-                    atomicAdd(&hcoarse[kCoarse - 1], (uint32_t)wave_clamp);
-                }
-            };
-            // One pass over the candidates: histogram, scan, and either the threshold (true) or a
-            // narrower window for the next pass (false).  The first pass, the only one in all but
-            // a few frames, is compiled with its window constants folded in.
-            auto pass = [&](auto first_tag) -> bool {
-                constexpr bool kFirst = decltype(first_tag)::value;
-                if (kFirst) {
-                    w.lo = 0;
-                    w.mode = 0;
-                    w.Dfix = 0;
-                    need = beam;
-                }
-                if (!kFirst) {  // rare: the single histogram is reused for a refined window
-                    lds_barrier();
-                    for (int i = tid; i < kFine; i += kThreads) hfine[i] = 0u;
-                    if (tid < kCoarse) hcoarse[tid] = 0u;
-                    lds_barrier();
-                }
-                int n_clamp = 0;  // this thread's candidates in the last bin
-                if constexpr (kCountAll) {
-                    if (D_stay != kAllOnes)
-                        hist_add_many(fc, w, D_stay, tid, -1, hfine, hcoarse, n_clamp);
-                    if (cD0 != kAllOnes)
-                        hist_add_many(fc, w, cD0, cI0, cT0, hfine, hcoarse, n_clamp);
-                } else {
-                    if (D_stay != kAllOnes) hist_add(fc, w, D_stay, tid, -1, hfine, hcoarse);
-                    if (cD0 != kAllOnes) hist_add(fc, w, cD0, cI0, cT0, hfine, hcoarse);
-                }
-                uint64_t nearest = kAllOnes;  // this thread's best candidate (score window only)
-                if (FLTOP_RARE(windowed)) {
-                    nearest = D_stay < cD0 ? D_stay : cD0;
-                }
-                if (FLOOR && kFirst && floored) {
-                    groups = 0;
-                    for (int m0 = kRegCand; m0 < M; m0 += 4) {
-                        // the four reads of each kind go out together
-                        int32_t tk4[4];
-                        double sc4[4];
-                        bool up4[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int k = fc.nb0 + ext_g + G * (m0 + u);
-                            up4[u] = ext_thread && k < K && m0 + u < M;
-                            const int at = up4[u] ? k : 0;
-                            tk4[u] = (int32_t)s_tok[at];
-                            sc4[u] = (double)s_lp[at];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const double src = (tk4[u] == ev.last) ? ev.pb : ev.ptot;
-                            sc4[u] = src + sc4[u] + lm_term<LM>(fc, ev.last, tk4[u]);
-                        }
-                        bool any_up = false;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const bool alive = up4[u] && sc4[u] > -INFINITY;
-                            up4[u] = alive && !(sc4[u] < floor);
-                            n_below += (alive && !up4[u]) ? 1 : 0;
-                            any_up |= up4[u];
-                        }
-                        uint64_t D4[4] = {kAllOnes, kAllOnes, kAllOnes, kAllOnes};
-                        if (__ballot(any_up) != 0) {  // rare in a long list
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                if (__ballot(up4[u]) == 0) continue;
-                                groups |= 1ull << ((m0 + u) >> gshift);
-                                if (up4[u] && !(((ev.kidmask >> (tk4[u] & 31)) & 1u) &&
-                                                kidset_has(kids, kKidSlots, ext_i, tk4[u]))) {
-                                    const uint64_t D = Rk - order_key(sc4[u]);
-                                    D4[u] = D;
-                                    if (windowed) nearest = D < nearest ? D : nearest;
-                                    hist_add_many(fc, w, D, ext_i, tk4[u], hfine, hcoarse, n_clamp);
-                                }
-                            }
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int row = m0 + u - kRegCand;
-                            if (row < drows) dcache[row * kThreads] = D4[u];
-                        }
-                    }
-                    const int wave_below = wave_inclusive_scan(n_below);
-                    if (lane == kWave - 1 && wave_below != 0) atomicAdd(&sh_below, wave_below);
-                } else if (FLTOP_RARE(M > kRegCand)) {
-                    for (int m = kRegCand; m < M; ++m) {
-                        int e, k;
-                        if (FLOOR && ((groups >> (m >> gshift)) & 1ull) == 0) continue;
-                        if (!cand_at(m, e, k)) continue;  // (and none at any later m)
-                        int se = 0;
-                        int32_t tk = 0;
-                        uint64_t D;
-                        const int row = m - kRegCand;
-                        if (!kFirst && row < drows) {
-                            D = dcache[row * kThreads];
-                            if (w.mode != 0 && D == w.Dfix) cand_name(e, k, se, tk);  // for its hash
-                        } else {
-                            D = cand_eval(e, k, se, tk);
-                            if (row < drows) dcache[row * kThreads] = D;
-                        }
-                        if (windowed) nearest = D < nearest ? D : nearest;
-                        if (D != kAllOnes)
-                            hist_add_many(fc, w, D, se, tk, hfine, hcoarse, n_clamp);
-                    }
-                    if constexpr (!kClampApart) add_clamped(n_clamp);
-                }
-                if constexpr (kClampApart) {
-                    if (kCountAll || M > kRegCand) add_clamped(n_clamp);
-                }
-                if (kFirst && windowed) {  // one LDS atomic per wavefront
-                    const uint64_t wave_nearest = wave_min_u64(nearest);
-                    if (lane == 0 && wave_nearest != kAllOnes)
-                        atomicMin((unsigned long long*)&sh_minD,
-                                  (unsigned long long)wave_nearest);
-                }
-                lds_barrier();
-                PHASE_MARK(2);
-                if (kFirst && windowed) {
-                    // the frame's best score, exactly; the window's floor in the same fp64
-                    // subtraction a plain implementation does, mapped back to a distance
-                    const uint64_t minD = sh_minD;
-                    if (minD != kAllOnes && minD <= Rk) {
-                        const double floor_score = key_value(Rk - minD) - a.beam_window;
-                        const uint64_t floor_key = order_key(floor_score);
-                        Dcut = floor_key <= Rk ? Rk - floor_key : 0;
-                    }
-                }
-                // every wave scans the histogram redundantly (results are uniform)
-                const int cs = (int)hcoarse[lane];
-                const int incl = wave_inclusive_scan(cs);
-                const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
-                // The two rows of fine bins looked at below -- the one with the first occupied
-                // bin (lanes 0..15) and the one in which the need-th candidate lies (lanes
-                // 16..31) -- are asked for together: one LDS round trip instead of two.
-                const uint64_t occ = __ballot(cs > 0);
-                const uint64_t cross = __ballot(incl >= need);
-                const int lmin = occ != 0 ? __ffsll((long long)occ) - 1 : 0;
-                const int lstar = cross != 0 ? __ffsll((long long)cross) - 1 : 0;
-                const int fine_row = (lane & 16) ? lstar : lmin;
-                const int fine_val = (int)hfine[fine_row * 16 + (lane & 15)];
-                if (kFirst) {
-                    const int below = FLOOR && floored ? sh_below : 0;
-                    pd_cand += (uint32_t)(total + below);
-                    pd_peak = max(pd_peak, (uint32_t)(total + below));
-                    // first occupied bin -> bound of the best candidate (window starts at 0)
-                    if (FLTOP_USUAL(occ != 0)) {
-                        const uint32_t f = (uint32_t)fine_val;
-                        const uint64_t occf = __ballot(f > 0 && lane < 16);
-                        const int bmin = lmin * 16 + (__ffsll((long long)occf) - 1);
-                        const uint64_t dmin = (w.sh > 0 && ((uint64_t)bmin >> (64 - w.sh)) != 0)
-                                                  ? kAllOnes
-                                                  : ((uint64_t)bmin << w.sh);
-                        kbest_key = dmin > Rk ? 0 : Rk - dmin;
-                    }
-                }
-                ++pd_pass;
-                if (FLTOP_RARE(total <= need)) {  // everything left in the window is kept
-                    selD = (w.mode == 0) ? kAllOnes : w.Dfix;
-                    selH = kAllOnes;
-                    return true;
-                }
-                // coarse bin holding the need-th candidate (lstar), then the fine bin inside it
-                // (its row sits in lanes 16..31; the row scan works within each 16 lanes)
-                const int above_c =
-                    __builtin_amdgcn_readlane(incl, lstar) - __builtin_amdgcn_readlane(cs, lstar);
-                const int fs = fine_val;
-                const int fincl = row_inclusive_scan(fs);
-                const uint64_t fcross =
-                    __ballot((lane & 48) == 16 && above_c + fincl >= need) >> 16;
-                const int fl = __ffsll((long long)fcross) - 1;
-                const int bstar = lstar * 16 + fl;
-                const int n_b = __builtin_amdgcn_readlane(fs, 16 + fl);
-                const int n_above = above_c + __builtin_amdgcn_readlane(fincl, 16 + fl) - n_b;
-                const int r = need - n_above;  // 1 <= r <= n_b
-                const bool clamp_bin = (bstar == kFine - 1) && (w.sh < kMaxShift);
-
-                if (FLTOP_USUAL(n_b == r)) {  // the boundary bucket is taken whole
-                    const uint64_t top = clamp_bin ? kAllOnes : bucket_top(w.lo, bstar, w.sh);
-                    if (w.mode == 0) {
-                        selD = top;
-                        selH = kAllOnes;
-                    } else {
-                        selD = w.Dfix;
-                        selH = top;
-                    }
-                    return true;
-                }
-                if (FLTOP_USUAL(n_b <= kExactCap)) {
-                    // ---- exact ranking of the boundary bucket by (distance, hash)
-                    ++pd_exact;
-                    if (D_stay != kAllOnes)
-                        boundary_add(fc, w, bstar, D_stay, tid, -1, &sh_blcount, bl_D, bl_h);
-                    if (cD0 != kAllOnes)
-                        boundary_add(fc, w, bstar, cD0, cI0, cT0, &sh_blcount, bl_D, bl_h);
-                    for (int m = kRegCand; m < M; ++m) {
-                        int e, k;
-                        if (FLOOR && ((groups >> (m >> gshift)) & 1ull) == 0) continue;
-                        if (!cand_at(m, e, k)) continue;  // (and none at any later m)
-                        int se = 0;
-                        int32_t tk = 0;
-                        uint64_t D;
-                        const int row = m - kRegCand;
-                        if (row < drows) {
-                            D = dcache[row * kThreads];
-                            // only a member of the boundary bucket is looked at further
-                            const bool maybe = w.mode != 0 ? D == w.Dfix
-                                                           : (D >= w.lo && window_bin(w, D) == bstar);
-                            if (!maybe) continue;
-                            cand_name(e, k, se, tk);
-                        } else {
-                            D = cand_eval(e, k, se, tk);
-                        }
-                        if (D != kAllOnes)
-                            boundary_add(fc, w, bstar, D, se, tk, &sh_blcount, bl_D, bl_h);
-                    }
-                    lds_barrier();
-                    if (tid < kWave) {
-                        const int n = min(sh_blcount, kExactCap);
-                        const bool mine = lane < n;
-                        const uint64_t myD = mine ? bl_D[lane] : 0;
-                        const uint64_t myH = mine ? bl_h[lane] : 0;
-                        int rank = 0, same = 0;
-                        for (int e = 0; e < n; ++e) {
-                            const uint64_t oD = bl_D[e], oH = bl_h[e];
-                            rank += (oD < myD || (oD == myD && oH < myH)) ? 1 : 0;
-                            same += (oD == myD && oH == myH) ? 1 : 0;
-                        }
-                        // the r-th best member (members that collide in both fields tie)
-                        if (mine && rank <= r - 1 && r - 1 < rank + same) {
-                            sh_selD = myD;
-                            sh_selH = myH;
-                        }
-                    }
-                    lds_barrier();
-                    selD = sh_selD;
-                    selH = sh_selH;
-                    PHASE_MARK(4);
-                    return true;
-                }
-                // ---- boundary bucket too large: narrow (or widen) the window
-                need = r;
-                if (clamp_bin) {
-                    w.lo = sat_add(w.lo, (uint64_t)(kFine - 1) << w.sh);
-                    w.sh = min(kMaxShift, w.sh + 8);
-                } else if (w.sh > 0) {
-                    w.lo = sat_add(w.lo, (uint64_t)bstar << w.sh);
-                    w.sh = max(0, w.sh - 10);
-                } else if (w.mode == 0) {
-                    // more than kExactCap candidates share one score: order them by hash
-                    w.Dfix = w.lo + (uint64_t)bstar;
-                    w.mode = 1;
-                    w.lo = 0;
-                    w.sh = kMaxShift;
-                } else {
-                    // identical score and identical hash (collision): keep them all
-                    selD = w.Dfix;
-                    selH = w.lo + (uint64_t)bstar;
-                    return true;
-                }
-                return false;
-            };
-            bool found = pass(std::true_type{});
-            // (hinted in every build: the 1024-thread build is 6% faster per frame with it)
-            for (int iter = 1; __builtin_expect(!found && iter < 40, 0); ++iter)
-                found = pass(std::false_type{});
-        }
-        if (FLTOP_RARE(Dcut < selD)) {  // the score window is narrower than the top-`beam` cut
-            selD = Dcut;
-            selH = kAllOnes;
-        }
-        PHASE_MARK(3);
-
-        // ---- compaction: selected candidates become the next beam ------------------
-        {
-            // the stay candidate and the first extension share one slot allocation per wave
-            uint64_t hh0 = 0, hhs = 0;
-            bool hv0 = false, hvs = false;
-            const bool sel_s =
-                D_stay != kAllOnes && is_selected(fc, selD, selH, D_stay, tid, -1, hhs, hvs);
-            const bool sel_0 =
-                cD0 != kAllOnes && is_selected(fc, selD, selH, cD0, cI0, cT0, hh0, hv0);
-            // places inside the wavefront from two ballots (the selected stays first, then the
-            // selected extensions): a handful of scalar and count instructions
-            const uint64_t m_s = __ballot(sel_s), m_0 = __ballot(sel_0);
-            const int n_s = __popcll(m_s);
-            const int wave_total = n_s + __popcll(m_0);
-            int base = 0;
-            if (wave_total > 0) {
-                if (lane == 0) base = atomicAdd(&sh_nnew, wave_total);
-                base = __builtin_amdgcn_readfirstlane(base);
-            }
-            const int slot_s = base + lanes_below(m_s, lane);
-            const int slot_0 = base + n_s + lanes_below(m_0, lane);
-            PHASE_MARK(9);
-            if (sel_s)
-                emit_stay<MB, kPrefetchStay>(fc, nxt, lkn, ccur, cnxt, newslot, slot_s, beam, tid, my_pb,
-                                             my_pnb, my_tot, sf);
-            if (sel_0)
-            {
-                if constexpr (kPrefetchStay)
-                    emit_ext_prefetched(fc, nxt, lkn, ccur, cnxt, slot_0, beam, t_base + t, cD0, cI0,
-                                        cT0, hh0, hv0, trie, trie_stride, &xs0);
-                else
-                    emit_ext(fc, nxt, lkn, ccur, cnxt, slot_0, beam, t_base + t, cD0, cI0, cT0, hh0,
-                             hv0, trie, trie_stride);
-            }
-        }
-        for (int m = kRegCand; m < M; ++m) {  // candidates beyond the register cache
-            if (FLOOR && ((groups >> (m >> gshift)) & 1ull) == 0) continue;
-            int e, k;
-            const bool there = cand_at(m, e, k);
-            bool sel = false;
-            int se = 0;
-            int32_t tk = 0;
-            uint64_t D = kAllOnes, hh = 0;
-            bool have_h = false;
-            if (there) {
-                const int row = m - kRegCand;
-                if (row < drows) {
-                    D = dcache[row * kThreads];
-                    if (D != kAllOnes && D <= selD) cand_name(e, k, se, tk);  // a contender
-                } else {
-                    D = cand_eval(e, k, se, tk);
-                }
-                if (D != kAllOnes && D <= selD)
-                    sel = is_selected(fc, selD, selH, D, se, tk, hh, have_h);
-            }
-            const uint64_t m_sel = __ballot(sel);
-            if (m_sel == 0) continue;
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&sh_nnew, __popcll(m_sel));
-            base = __builtin_amdgcn_readfirstlane(base);
-            if (sel)
-                emit_ext(fc, nxt, lkn, ccur, cnxt, base + lanes_below(m_sel, lane), beam, t_base + t,
-                         D, se, tk, hh, have_h, trie, trie_stride);
+            constexpr bool floored = false;
+#include "fltop_beam_frame.inc"
         }
         // the links phase reads what other threads have just emitted: LDS always, and in
         // kColdGlobal builds their stores to global memory too
@@ -1861,7 +1391,7 @@ void beam_kernel(BeamArgs a) {
         }
         if (tid == 0) {
             sh_minD = kAllOnes;
-            if (FLOOR) {
+            if (floored_frame) {
                 sh_floor = kAllOnes;
                 sh_toptok = INT32_MAX;
                 sh_below = 0;
