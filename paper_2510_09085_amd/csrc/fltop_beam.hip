@@ -42,6 +42,7 @@
 // candidate mapping where frames hold hundreds to thousands of candidates, and two with a
 // tighter register budget for batches that fill the chip, where instruction issue and
 // residency count instead of one frame's latency (see launch_beam).
+#include <cmath>
 #include <type_traits>
 
 #include "fltop_internal.h"
@@ -1773,16 +1774,26 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // (large vocabulary: eight wavefronts per utterance while the whole batch is resident that
     // way, two workgroups per CU, four beyond: B = 1024, V = 1024: 143 M frames/s against
     // 120 M; B = 512: 93 M against 111 M)
-    // Builds with the score floor where a frame can reach kFlooredFrom candidates per thread at
-    // all (a full beam, every token kept); elsewhere the code for it only costs registers
-    // (measured: beam 1000 with the 4 best tokens 6% slower, V = 32 unpruned 4%).
-    const int per_entry = (huge_beam ? kThreadsHuge : kThreadsLarge) / p.beam;
+    // Which survivor lists to expect.  A threshold R > 0 keeps a share of the vocabulary that falls
+    // with R: `likely` is what a frame with competing tokens keeps of it, fitted to where the builds
+    // for long lists begin to pay on this repository's emissions (tokens per threads of an entry;
+    // time with short lists assumed / with long ones, 160 random calls: R = 0.1: 447 0.96, 1670
+    // 1.08; R = 0.01: 16 0.97, 32 1.00, 64 1.02, 113 1.05, 900 1.42; R = 0.003: 16 1.09; R = 0.001:
+    // 10 1.03, 16 1.10, 32 1.21).  Results do not depend on it.
+    const double share =
+        p.rel_threshold > 0.0f ? 0.1 * std::pow(0.01 / (double)p.rel_threshold, 1.25) : 1.0;
+    const double likely = fmin((double)kept_at_most, (double)V * fmin(1.0, share));
+    const int per_entry = (huge_beam ? kThreadsHuge : kThreadsLarge) / p.beam;  // of a full beam
+    const int entry_threads = per_entry > 0 ? per_entry : 1;
+    // Long: some thread has kFlooredFrom candidates.
     const bool long_lists =
-        kept_at_most > kRegK && kept_at_most > (kFlooredFrom - 1) * (per_entry > 0 ? per_entry : 1);
-    // A search that keeps every token, but of a vocabulary that gives no thread that many: up to
-    // three candidates per thread, of which most lie beyond the histogram's window (see kCountAll;
-    // the 1024-thread build, which gets there with at most six tokens per frame, gains nothing).
-    const bool whole_lists = !long_lists && p.rel_threshold == 0.0f;
+        kept_at_most > kRegK && likely > (double)((kFlooredFrom - 1) * entry_threads);
+    // Whole: every token is kept, of a vocabulary that gives no thread that many, or a static
+    // top-N is filled: up to three candidates per thread, of which most lie beyond the histogram's
+    // window (see kCountAll; the 1024-thread build, which gets there with at most six tokens per
+    // frame, gains nothing).
+    const bool whole_lists = !long_lists && (p.rel_threshold == 0.0f ||
+                                             (!large_beam && likely > (double)entry_threads));
     const bool tiny_state = p.beam <= kBeamTiny && carried == nullptr;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
