@@ -37,7 +37,8 @@
 //    mapped to different wavefronts so that they are evaluated side by side, and
 //    the end-of-frame clean-up is done by the wavefronts that have no links to set.
 //
-// The kernel is built several times over (workgroup size, beam capacity, register budget):
+// The kernel is built several times over (workgroup size, beam capacity, register budget, and
+// the length of the survivor lists it is to expect):
 // four wavefronts for the frames of a pruned small vocabulary, eight with an entry-major
 // candidate mapping where frames hold hundreds to thousands of candidates, and two with a
 // tighter register budget for batches that fill the chip, where instruction issue and
@@ -68,7 +69,10 @@ constexpr int kExactCap = 64;
 constexpr int kMaxShift = 54;  // kFine << kMaxShift covers all 64-bit distances
 constexpr int kRegK = kInlineSurvivors;  // survivors kept in registers
 constexpr int kRegCand = 1;              // extension candidates kept in registers per thread
-constexpr int kFlooredFrom = 4;          // candidates per thread from which a frame gets a score floor
+// Candidates per thread from which a frame gets a score floor (times at 2 / 3 / 4 / 8, us: 64
+// utterances x 500 frames, V = 32, beam 32, every token kept: 2528 / 2279 / 2278 / 2279; 150 frames,
+// beam 100: 1107 / 1113 / 1112 / 1805; 128 x 400, V = 1024, beam 64, R = 0.01: 805 / 781 / 773 / 797).
+constexpr int kFlooredFrom = 4;
 constexpr int kChunk = 32;               // frame headers staged per chunk
 constexpr int kWaypoints = 256;
 constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull;
@@ -504,7 +508,7 @@ __device__ __forceinline__ double lp_of(const FrameCtx<MB>& f, int32_t tok) {
 
 // What the kernel is built for, as to the survivor lists of the frames it will meet (512 and
 // 1024 threads; see launch_beam): short ones, as a threshold leaves them, every token of a
-// vocabulary that gives a thread two or three candidates, or lists long enough for a score floor.
+// vocabulary that gives a thread up to three candidates, or lists long enough for a score floor.
 enum : int { kListsShort = 0, kListsWhole = 1, kListsLong = 2 };
 
 // The LM flavour is a kernel template parameter: with one kernel serving all three, the
@@ -694,9 +698,10 @@ __device__ __forceinline__ void hist_add(const FrameCtx<MB>& f, const Window& w,
     atomicAdd(&hcoarse[bin >> 4], 1u);
 }
 
-// The same for the candidates beyond the register cache, of which a frame may have
-// thousands (and for all of a thread's, see kCountAll).  All that lie beyond the window share the last bin, and one LDS word cannot
-// take that many atomics quickly: those are counted in a register (`n_clamp`) instead.
+// The same for the candidates beyond the register cache, of which a frame may have thousands
+// (and for all of a thread's, see kCountAll).  All that lie beyond the window share the last
+// bin, and one LDS word cannot take that many atomics quickly: those are counted in a register
+// (`n_clamp`) instead.
 template <int MB>
 __device__ __forceinline__ void hist_add_many(const FrameCtx<MB>& f, const Window& w, uint64_t D,
                                               int se, int32_t tk, uint32_t* hfine,
@@ -888,7 +893,7 @@ void beam_kernel(BeamArgs a) {
     // builds with 512 threads or more take a thread's candidates from one entry (see EntryView)
     constexpr bool kEntryMajor = THREADS >= kThreadsLarge;
     static_assert(kEntryMajor || LISTS == kListsShort, "the others are made for the entry-major mapping");
-    constexpr bool FLOOR = LISTS == kListsLong;  // with the score floor (see `floored`)
+    constexpr bool FLOOR = LISTS == kListsLong;  // with the score floor (see `floored_frame`)
     static_assert(kEntryMajor || !kColdGlobal, "the largest capacity has no children lists");
     // Builds with four wavefronts read what a staying entry carries over together with its
     // masses (measured: cfg 3 -1.7%); the larger builds, shorter of registers, read it when the
@@ -926,7 +931,7 @@ void beam_kernel(BeamArgs a) {
     __shared__ FrameHdr ring[kChunk];
     __shared__ uint64_t sh_selD, sh_selH, sh_kbest;
     __shared__ uint64_t sh_minD;  // smallest distance (= best score) among a frame's candidates
-    // frames with a score floor (see `floored`)
+    // frames with a score floor (see `floored_frame`)
     __shared__ uint64_t sh_floor;  // complement of the largest of the entries' own distances
     __shared__ int32_t sh_toptok;  // non-blank token with the frame's top emission, if there is one
     __shared__ int32_t sh_below;   // candidates below the floor
@@ -1209,7 +1214,8 @@ void beam_kernel(BeamArgs a) {
             t = t_end;
             continue;
         }
-        const int nb0 = hd.first[0].tok == 0 ? 1 : 0;  // survivors ascend by token: the blank, if kept, is the first
+        // survivors ascend by token: the blank, if kept, is the first
+        const int nb0 = hd.first[0].tok == 0 ? 1 : 0;
         // Frames with thousands of candidates: nearly all of them lie far below the beam's cut.
         // With the beam full, every entry i stands for one candidate of its own, the better of
         // "i stays" and "i extended by the frame's top token": that is `beam` different

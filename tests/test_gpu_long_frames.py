@@ -2,6 +2,7 @@
 changes its way of going through them: the number of candidates per thread from which a frame
 gets a score floor, batches of four with a remainder, more than 64 and more than 128 numbers per
 thread, and each beam capacity.  Against the oracle, statistics included."""
+import numpy as np
 import pytest
 import torch
 
@@ -28,3 +29,53 @@ def test_long_survivor_lists(oracle_lib, V, beam, T, options):
     check_case(torch.device("cuda:0"), oracle_lib, lp, ln, beam, 0.0,
                V - 3 if options == "top_n" else 0, 12.0 if options == "window" else 0.0,
                f"V{V} beam{beam} {options}", lm=lm, lm_weight=0.7, insertion_bonus=0.3)
+
+
+def _decode_and_compare(oracle_lib, lp, beam, label, **more):
+    from test_gpu_ties import check_case
+    ln = np.full(lp.shape[0], lp.shape[1], dtype=np.int32)
+    return check_case(torch.device("cuda:0"), oracle_lib, lp, ln, beam, 0.0, 0, 0.0, label, **more)
+
+
+@pytest.mark.parametrize("with_lm", [False, True])
+@pytest.mark.parametrize("V,beam", [(100, 32), (1030, 32), (40, 300), (300, 600)])
+def test_tokens_without_mass_in_a_long_list(oracle_lib, V, beam, with_lm):
+    """R = 0 keeps tokens of log-prob -inf too; they are no candidates and are not counted.  A
+    third of all tokens, a frame's top token included where it is the blank, and whole columns;
+    the table has pairs of log-prob -inf as well."""
+    rng = np.random.default_rng(V + beam)
+    B, T = 2, 14
+    lp = synth.random_emissions(V, B, T, V, flat=1.0)
+    lp[rng.random(lp.shape) < 0.33] = -np.inf
+    lp[:, 5, 1:] = -np.inf          # only the blank has mass
+    lp[:, 9, 0] = -np.inf           # the blank has none
+    lp[:, :, 3] = -np.inf
+    lp[:, 5, 0] = -0.25
+    more = {}
+    if with_lm:
+        lm = synth.make_bigram_lm(V, seed=beam)
+        lm[rng.random(lm.shape) < 0.2] = -np.inf
+        more = dict(lm=lm, lm_weight=0.7, insertion_bonus=0.3)
+    _decode_and_compare(oracle_lib, lp, beam, f"V{V} beam{beam} -inf", **more)
+
+
+@pytest.mark.parametrize("V,beam,T,with_lm", [(1026, 32, 4, False), (64, 128, 6, True),
+                                              (64, 128, 6, False), (300, 64, 4, True)])
+def test_more_utterances_than_compute_units(oracle_lib, V, beam, T, with_lm):
+    """One to two utterances per compute unit: a build whose distance cache has a single row, so
+    nearly every candidate is evaluated again by the later passes (table in LDS and in memory)."""
+    B = torch.cuda.get_device_properties(0).multi_processor_count + 8
+    lp = synth.random_emissions(V, B, T, V, flat=1.5)
+    lm = synth.make_bigram_lm(V, seed=beam) if with_lm else None
+    _decode_and_compare(oracle_lib, lp, beam, f"V{V} beam{beam} B{B}", lm=lm, lm_weight=0.7,
+                        insertion_bonus=0.3)
+
+
+@pytest.mark.parametrize("B", [2, 264])
+def test_ties_beyond_64_candidates_per_thread(oracle_lib, B):
+    """Emissions in steps of 1/2: many candidates of one score at the cut, so the selection goes
+    on by hash, with candidate numbers taken in groups of two."""
+    T = 4 if B == 2 else 3
+    lp = (np.round(synth.random_emissions(7, B, T, 1030, flat=1.0) * 2) / 2).astype(np.float32)
+    tied, _ = _decode_and_compare(oracle_lib, lp, 32, f"quantised B{B}")
+    assert tied > 0
