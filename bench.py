@@ -2,12 +2,14 @@
 """Benchmark of the FLToP CTC decode path on one MI355X.
 
 A "step" is one call of fltop_ctc_decode (prune stage + beam search + best prefix) over
-one batch of seeded synthetic emissions that already sit in HBM.  Prints ONE JSON line.
+one batch of seeded synthetic emissions that already sit in HBM.  Prints ONE JSON line of a few
+kilobytes; the whole record (some 20 KB) goes to stderr as one JSON line behind "record: ", and
+with --record to a file.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload cfg3_varlen256] [--rel-threshold 0.01]
 
 The headline workload is the largest of the five named ones (256 utterances of 250..1500
-frames, beam 100: one workgroup per compute unit); `per_config` in the same line times every
+frames, beam 100: one workgroup per compute unit); `per_config` in the same line gives every
 named workload at every threshold it lists, GPU and CPU oracle side by side.
 
 Two helper modes serve the profiles kept under profiles/:
@@ -63,6 +65,8 @@ def parse_args():
     ap.add_argument("--probe-replicas", type=int, default=1,
                     help="with --counter-probe search: decode the workload's utterances this "
                          "many times over in one batch (large-batch regime)")
+    ap.add_argument("--record", metavar="FILE", default=None,
+                    help="also write the whole record there")
     return ap.parse_args()
 
 
@@ -814,6 +818,28 @@ def summarise(argv):
         sys.exit(2)
 
 
+# what the printed line leaves to the whole record
+RECORD_ONLY = ("emission_read_all_workloads", "cfg2_extras", "paper_context")
+
+
+def headline(result):
+    """The record as it is printed: everything but the long lists, `per_config` down to its times
+    and rates (a line that a reader of the last few kilobytes of output still finds whole)."""
+    line = {k: v for k, v in result.items() if k not in RECORD_ONLY}
+    if "per_config" in line:
+        rows = []
+        for c in line["per_config"]:
+            row = {"workload": c["workload"], "rel_threshold": c["rel_threshold"],
+                   "ms_per_step": c["ms_per_step"],
+                   "M_frames_per_s": round(c["frames_per_s"] / 1e6, 2)}
+            if "cpu_oracle" in c:
+                row["oracle_k_frames_per_s"] = round(
+                    c["cpu_oracle"]["all_cores"]["frames_per_s"] / 1e3, 2)
+            rows.append(row)
+        line["per_config"] = rows
+    return line
+
+
 def main():
     args = parse_args()
     if args.summarise:
@@ -954,7 +980,12 @@ def main():
         result["cpu_baseline"] = cpu_baseline(synth, w, r)
         result["gpu_vs_cpu_oracle"] = round(fps / result["cpu_baseline"]["value"], 1)
 
-    print(json.dumps(result))
+    if args.record:
+        with open(args.record, "w") as fh:
+            json.dump(result, fh, indent=1)
+            fh.write("\n")
+    print("record: " + json.dumps(result), file=sys.stderr, flush=True)
+    print(json.dumps(headline(result)))
 
 
 if __name__ == "__main__":
