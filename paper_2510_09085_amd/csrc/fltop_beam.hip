@@ -906,14 +906,17 @@ void beam_kernel(BeamArgs a) {
     // frames, V = 32, beam 200, R = 0.1: 609 -> 623 us; V = 100, beam 8, table in memory: 605 -> 627).
     constexpr bool kCountAll = LISTS != kListsShort;
     // Where the last bin's count is handed over: inside the block of a thread's later candidates,
-    // which the usual frame of a pruned small vocabulary jumps over, or behind it.  A second
-    // branch there costs the 256- and 128-thread builds 2-3% (64 utterances x 500 frames, V = 32,
-    // beam 32: 625 against 644 us; 4096 of them: 2287 against 2327 us).  The 256-thread build for
-    // batches of large vocabularies beyond the chip, whose frames mostly have later candidates,
-    // is faster with it (600 utterances x 100 frames, V = 1024: 668 against 698 us; with a table in
-    // memory 748 against 740 us, so not there).
+    // which the usual frame of a pruned small vocabulary jumps over, or behind it, which is one
+    // more branch for that frame.  It costs the 256- and 128-thread builds without a table 2-3% (64
+    // utterances x 500 frames, V = 32, beam 32: 625 against 644 us; 4096 of them: 2287 against
+    // 2327); with a table in LDS they are 0.2-2% faster with it (128 x 500, beam 64: 692 against
+    // 690 us; 1500 x 60, beam 100, R = 0.001: 1238 against 1213).  The 256-thread build for batches
+    // of large vocabularies beyond the chip, whose frames mostly have later candidates, is faster
+    // with it (600 x 100, V = 1024: 698 against 668 us), with a table in memory slower (740
+    // against 748).
     constexpr bool kClampApart =
-        kCountAll || (THREADS == kThreadsSmall && WAVES == 4 && LM != kLmGlobal);
+        kCountAll || (!kEntryMajor && LM == kLmLds) ||
+        (THREADS == kThreadsSmall && WAVES == 4 && LM == kLmNone);
     // Which way a uniform branch of the frame loop usually goes, for the block layout of the
     // four-wavefront builds: a lone wavefront per SIMD pays for every taken branch, and with the
     // usual path laid out straight a frame is 2-4% shorter (the set below was chosen by timing
