@@ -79,3 +79,27 @@ def test_ties_beyond_64_candidates_per_thread(oracle_lib, B):
     lp = (np.round(synth.random_emissions(7, B, T, 1030, flat=1.0) * 2) / 2).astype(np.float32)
     tied, _ = _decode_and_compare(oracle_lib, lp, 32, f"quantised B{B}")
     assert tied > 0
+
+
+# (V, beam, top_n, the threshold at which the launcher goes over to another build): 512 threads with
+# 128 entries, with 512 entries, 1024 threads, and from lists of a static top-N to short ones
+SWITCHES = [(1024, 32, 0, 0.01829), (32, 200, 0, 0.00605), (40, 600, 0, 0.01259),
+            (1024, 64, 16, 0.07676)]
+
+
+@pytest.mark.parametrize("with_lm", [False, True])
+@pytest.mark.parametrize("side", [0.99, 1.01])
+@pytest.mark.parametrize("V,beam,top_n,r", SWITCHES)
+def test_thresholds_at_which_the_build_changes(oracle_lib, V, beam, top_n, r, side, with_lm):
+    """Frames of every length meet either build: some led by one token, some with many alike."""
+    from test_gpu_ties import check_case
+    rng = np.random.default_rng(V + beam)
+    B, T = 3, 24
+    x = rng.standard_normal((B, T, V)) * rng.choice([0.5, 2.0], size=(B, T, 1))
+    lead = rng.random((B, T)) < 0.4
+    x[..., 0][lead] += 9.0
+    lp = synth._log_softmax64(x).astype(np.float32)
+    ln = np.array([T, T - 5, T], dtype=np.int32)
+    lm = synth.make_bigram_lm(V, seed=beam) if with_lm else None
+    check_case(torch.device("cuda:0"), oracle_lib, lp, ln, beam, float(np.float32(r * side)), top_n,
+               0.0, f"V{V} beam{beam} r{r * side:.5f}", lm=lm, lm_weight=0.6, insertion_bonus=0.2)
