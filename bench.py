@@ -636,6 +636,10 @@ PHASES = (  # (index in fltop_stats.phase_clocks, what the span covers), in pipe
     (5, "emit into the next beam, trie stores, barrier 2"),
     (10, "parent / children links of the new beam"),
     (6, "housekeeping, a following run of blank-only frames, barrier 3"),
+    (11, "light frames: candidates evaluated, barrier 1"),
+    (12, "light frames: candidates counted into bins, barrier 2"),
+    (13, "light frames: places among the bins"),
+    (15, "light frames: moves into the next beam, barrier 3"),
     (7, "blank-only runs at the start of a 32-frame header chunk"),
 )
 
@@ -680,7 +684,7 @@ def counter_probe(args, torch, binding, synth, dev):
     r = args.rel_threshold
     out = {"probe": args.counter_probe, "workload": w.name, "rel_threshold": r}
     srcs = ["fltop_prune.hip", "fltop_internal.h"] if args.counter_probe == "prune" else \
-        ["fltop_beam.hip", "fltop_beam_frame.inc", "fltop_internal.h"]
+        ["fltop_beam.hip", "fltop_beam_frame.inc", "fltop_beam_light.inc", "fltop_internal.h"]
     if args.counter_probe == "prune":
         copies = 3
         job = Job(torch, binding, synth, w, dev, copies=copies)

@@ -302,12 +302,75 @@ __device__ __forceinline__ double log1p_unit(double u) {  // 0 <= u <= 1
     return upper ? 0.6931471803691238 + body : body;
 }
 
+// Skipped by wavefronts in which no lane has two operands.
 __device__ __forceinline__ double lse2(double a, double b) {
     if (a == -INFINITY) return b;
     if (b == -INFINITY) return a;
     const double hi = a > b ? a : b;
     const double lo = a > b ? b : a;
     return hi + log1p_unit(exp_nonpositive(lo - hi));
+}
+
+// The same from the same series, without branches (an operand may be -inf, or both), with a reciprocal
+// and two Newton steps for the quotient, whose rounding error is carried along as above, and with the
+// coefficients kept in vector registers (40 of them): the compiler's own choice for a polynomial
+// copies every coefficient into the accumulator first.  Taken by light frames.
+__device__ __forceinline__ double fma_regs(double x, double y, double z) {
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(x), "v"(y), "v"(z));
+    return d;
+}
+
+__device__ __forceinline__ double lse2_any(double a, double b) {
+    const double hi = fmax(a, b);
+    const double x = fmax(fmin(a, b) - hi, -800.0);  // (exp(-800) is 0; the difference may be NaN)
+    const double n = rint(x * 1.4426950408889634);
+    double r = fma(-n, 0.6931471803691238, x);
+    r = fma(-n, 1.9082149292705877e-10, r);
+    double p = 1.6059043836821613e-10;
+    p = fma_regs(p, r, 2.08767569878681e-09);
+    p = fma_regs(p, r, 2.505210838544172e-08);
+    p = fma_regs(p, r, 2.755731922398589e-07);
+    p = fma_regs(p, r, 2.7557319223985893e-06);
+    p = fma_regs(p, r, 2.48015873015873e-05);
+    p = fma_regs(p, r, 0.0001984126984126984);
+    p = fma_regs(p, r, 0.001388888888888889);
+    p = fma_regs(p, r, 0.008333333333333333);
+    p = fma_regs(p, r, 0.041666666666666664);
+    p = fma_regs(p, r, 0.16666666666666666);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    const double u = ldexp(p, (int)n);
+    const double w = 1.0 + u;
+    const double c = u - (w - 1.0);
+    const bool upper = w > 1.4142135623730951;
+    const double f = upper ? fma(w, 0.5, -1.0) : w - 1.0;
+    // f / (2 + f): reciprocal, two Newton steps, and the quotient's rounding error carried along
+    const double den = 2.0 + f;
+    double y = __builtin_amdgcn_rcp(den);
+    y = fma(fma(-den, y, 1.0), y, y);
+    y = fma(fma(-den, y, 1.0), y, y);
+    const double s = f * y;
+    const double s_lo = fma(-s, den, f) * y;
+    const double z = s * s;
+    double q = 0.08;
+    q = fma_regs(q, z, 0.08695652173913043);
+    q = fma_regs(q, z, 0.09523809523809523);
+    q = fma_regs(q, z, 0.10526315789473684);
+    q = fma_regs(q, z, 0.11764705882352941);
+    q = fma_regs(q, z, 0.13333333333333333);
+    q = fma_regs(q, z, 0.15384615384615385);
+    q = fma_regs(q, z, 0.18181818181818182);
+    q = fma_regs(q, z, 0.2222222222222222);
+    q = fma_regs(q, z, 0.2857142857142857);
+    q = fma_regs(q, z, 0.4);
+    q = fma_regs(q, z, 0.6666666666666666);
+    const double cw = (upper ? 0.5 * c : c) * __builtin_amdgcn_rcp(1.0 + f);
+    double tail = fma(s * z, q, 2.0 * s_lo + cw);
+    tail += upper ? 1.9082149292705877e-10 : 0.0;
+    const double body = 2.0 * s + tail;
+    return hi + (body + (upper ? 0.6931471803691238 : 0.0));
 }
 
 // number of set bits of `mask` below this lane's own position
@@ -359,6 +422,16 @@ __device__ __forceinline__ int wave_inclusive_scan(int v0) {
     v1 += dpp_or_zero<0x142, 0xa>(v1);
     v1 += dpp_or_zero<0x143, 0xc>(v1);
     return v1;
+}
+
+// Inclusive prefix sum of floats over lanes 0..31 (the same over lanes 32..63).
+__device__ __forceinline__ float row32_inclusive_sum(float v) {
+    v += __int_as_float(dpp_or_zero<0x111, 0xf>(__float_as_int(v)));
+    v += __int_as_float(dpp_or_zero<0x112, 0xf>(__float_as_int(v)));
+    v += __int_as_float(dpp_or_zero<0x114, 0xf>(__float_as_int(v)));
+    v += __int_as_float(dpp_or_zero<0x118, 0xf>(__float_as_int(v)));
+    v += __int_as_float(dpp_or_zero<0x142, 0xa>(__float_as_int(v)));
+    return v;
 }
 
 // Minimum of an unsigned value over the wavefront, returned in every lane: pairwise
@@ -875,11 +948,41 @@ __device__ __forceinline__ void emit_ext_prefetched(const FrameCtx<MB>& f, BeamS
     publish_hash(lkn, hh, slot);
 }
 
+// Light frames (fltop_beam_light.inc).
+constexpr int kLightBins = 256;  // bins of their selection, 16 bits each
+constexpr int kLightRounds = 3;  // most extensions per thread
+typedef unsigned short Ushort2 __attribute__((ext_vector_type(2)));
+// Their tables: the bins, then a bitmap over the hashes of the prefixes that entered.
+template <int THREADS>
+struct LightTables {
+    static constexpr int kWords = THREADS == kThreadsSmall ? 512 : 256;  // cleared by one store of each thread
+    static constexpr int kFresh = THREADS == kThreadsSmall ? 256 : 128;
+    static_assert(kLightBins / 2 + kFresh <= kWords, "bins and bitmap");
+    static __device__ __forceinline__ int fresh_word(uint64_t h) {
+        return kLightBins / 2 + ((int)((uint32_t)h >> 5) & (kFresh - 1));
+    }
+};
+
+// Value of another lane, the same one for the whole wavefront.
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int from) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, from);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), from);
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ double lane_value(double v, int from) {
+    return __longlong_as_double((long long)lane_value((uint64_t)__double_as_longlong(v), from));
+}
+
+// State of a beam's parent links between frames: places of the parents, and the children lists that
+// the general path needs; or what a light frame leaves: the parents' places in the beam before, -2
+// for a parent that was not there.
+enum : int { kLinksBuilt = 0, kLinksCoded = 1 };
+
 // WAVES = wavefronts per SIMD the register budget is cut for: 2 leaves the allocator all it
 // asks for (no spills: the fastest single workgroup); 3 and 4 spill a few registers (each
 // frame some per cent slower) so that more utterances are resident when the batch has more
 // workgroups than the chip can hold at 2.
-// LISTS: the survivor lists it is made for (kListsShort for builds with 256 and 128 threads).
+// LISTS: the survivor lists it is made for.
 template <int LM, int THREADS, int MB, int WAVES, int LISTS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 void beam_kernel(BeamArgs a) {
@@ -892,7 +995,7 @@ void beam_kernel(BeamArgs a) {
     static_assert(THREADS >= MB, "one thread per beam entry");
     // builds with 512 threads or more take a thread's candidates from one entry (see EntryView)
     constexpr bool kEntryMajor = THREADS >= kThreadsLarge;
-    static_assert(kEntryMajor || LISTS == kListsShort, "the others are made for the entry-major mapping");
+    static_assert(kEntryMajor || LISTS != kListsLong, "the floor is made for the entry-major mapping");
     constexpr bool FLOOR = LISTS == kListsLong;  // with the score floor (see `floored_frame`)
     static_assert(kEntryMajor || !kColdGlobal, "the largest capacity has no children lists");
     // Builds with four wavefronts read what a staying entry carries over together with its
@@ -904,7 +1007,7 @@ void beam_kernel(BeamArgs a) {
     // and atomics on one word queue up (64 utterances x 500 frames, V = 32, every token kept: 2354
     // -> 2270 us).  Frames of short lists have few there and pay for the wavefront's sum (64 x 500
     // frames, V = 32, beam 200, R = 0.1: 609 -> 623 us; V = 100, beam 8, table in memory: 605 -> 627).
-    constexpr bool kCountAll = LISTS != kListsShort;
+    constexpr bool kCountAll = kEntryMajor && LISTS != kListsShort;
     // Where the last bin's count is handed over: inside the block of a thread's later candidates,
     // which the usual frame of a pruned small vocabulary jumps over, or behind it, which is one
     // more branch for that frame.  It costs the 256- and 128-thread builds without a table 2-3% (64
@@ -941,6 +1044,15 @@ void beam_kernel(BeamArgs a) {
     __shared__ int32_t sh_nnew, sh_blcount, sh_best;
     __shared__ unsigned long long sh_stat[8];
     __shared__ __align__(16) int32_t newslot[kMaxBeam];  // old beam index -> new beam index of an entry that stays
+    // (the builds for more utterances than that have no LDS and registers to spare for them)
+    constexpr bool kLight = LISTS == kListsShort && ((THREADS == kThreadsSmall && WAVES == 2) || (THREADS == kThreadsDense && MB == kBeamTiny));
+    using Tables = LightTables<THREADS>;
+    // light frames: bins, bitmap of the prefixes that entered, and a word per lane that nobody reads
+    // (two of each, the idle one is cleared meanwhile)
+    __shared__ __align__(16) uint32_t light_tables[2][kLight ? Tables::kWords + kWave : 4];
+    // light frame in which entry i's extension by non-blank survivor k was last merged, at
+    // (k << light_lg) + i
+    __shared__ uint32_t light_kill[kLight ? kLightRounds * (kThreads - kWave) : 4];
     extern __shared__ __align__(16) unsigned char dyn_lds[];
 
     const int tid = threadIdx.x;
@@ -960,6 +1072,9 @@ void beam_kernel(BeamArgs a) {
     // evaluating the candidate again (row j, this thread's place = its candidate number
     // kRegCand + j).  A thread only ever reads what it wrote itself.
     uint64_t* const dcache = reinterpret_cast<uint64_t*>(dyn_lds + a.dcache_off) + tid;
+    // light frames: scores of the candidates, the stays, then the extensions of each round (at most
+    // 5 / 2 of the threads, which is less than the rows of the distance cache, see launch_beam)
+    double* const light_score = reinterpret_cast<double*>(dyn_lds + a.dcache_off);
     const int drows = a.dcache_rows;
 
     StreamState<MB>* const carried =
@@ -1020,6 +1135,10 @@ void beam_kernel(BeamArgs a) {
         }
     }
     if (tid < 8) sh_stat[tid] = 0ull;
+    if constexpr (kLight) {
+        for (int i = tid; i < 2 * (Tables::kWords + kWave); i += kThreads) (&light_tables[0][0])[i] = 0u;
+        for (int i = tid; i < kLightRounds * (kThreads - kWave); i += kThreads) light_kill[i] = 0u;
+    }
     if (carried) {  // the beam as the previous chunk left it
         __syncthreads();  // the link arrays were just preset by other threads
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&carried->slab);
@@ -1053,16 +1172,6 @@ void beam_kernel(BeamArgs a) {
         __syncthreads();
     }
 
-    FrameCtx<MB> fc;
-    fc.dense_lp = dense_lp;
-    fc.s_tok = s_tok;
-    fc.s_lp = s_lp;
-    fc.lm_lds = (LdsFloatPtr)lm_s;
-    fc.lm_glb = a.lm_table;
-    fc.lm_alpha = a.lm_alpha;
-    fc.lm_beta = a.lm_beta;
-    fc.V = V;
-
     // non-blank survivors up to which no thread has kFlooredFrom candidates (full beam)
     const int floored_above = (kFlooredFrom - 1) * (kThreads / beam);
     int mapped_for = -1;  // kEntryMajor: the beam size the thread -> entry mapping was made for
@@ -1083,6 +1192,51 @@ void beam_kernel(BeamArgs a) {
         kmax_v = carried->kmax;
         kmin_v = carried->kmin;
     }
+
+    // Light frames: wavefronts [0, light_stay_waves) take the entries that stay; behind them sit
+    // light_blocks blocks of 1 << light_lg extensions, one block per non-blank survivor and round.
+    int links_are = kLinksBuilt;
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const bool windowed = a.beam_window > 0.0;
+    int light_x = 0;         // which of the two histograms and bitmaps this light frame uses
+    uint32_t light_tag = 0;  // number of the light frame
+    int light_lg = 0, light_stay_waves = 1, light_blocks = 0;
+    float light_spread = 0.0f, light_scale = 0.0f;
+    const double light_slack = lm_ub + 1.0986122886681098 + 1e-3;
+    // what the bins cover beyond the spread of the beam: how far the cut may fall in one frame (a table
+    // spreads the scores); grows where that was not enough
+    float light_margin = (float)light_slack + (has_lm ? 8.0f : 0.5f);
+    if constexpr (kLight) {
+        while ((1 << light_lg) < beam) ++light_lg;
+        light_stay_waves = ((1 << light_lg) + kWave - 1) / kWave;
+        light_blocks = (kThreads - light_stay_waves * kWave) >> light_lg;
+    }
+    // place of an entry's parent in the beam (-1: not there)
+    auto parent_place = [&](int j, uint64_t want, int32_t depth) -> int {
+        const int32_t code = links[gen].par[j];
+        if (links_are != kLinksCoded) return code;
+        if (code >= 0) return newslot[code];
+        if (depth == 0 ||
+            ((light_tables[light_x ^ 1][Tables::fresh_word(want)] >> ((uint32_t)want & 31u)) & 1u) == 0)
+            return -1;
+        int p = -1;
+        for (int v = 0; v < n_live; ++v)
+            if (slab[gen].h[v] == want) p = v;
+        return p;
+    };
+    // parent places and children lists from what a light frame left
+    auto build_links = [&](Links<MB>* lk) {
+        if (tid < n_live) {
+            const ColdRef<MB> c{&slab[gen], nullptr};
+            const int p = parent_place(tid, c.hp(tid), c.plen(tid));
+            lk->par[tid] = p;
+            if (p >= 0) {
+                lk->next_kid[tid] = atomicExch(&lk->first_kid[p], tid);
+                atomicOr(&lk->kidmask[p], 1u << (slab[gen].last[tid] & 31));
+            }
+        }
+        links_are = kLinksBuilt;
+    };
 
     // Statistics of this utterance live in LDS, not in 64-bit registers that every thread would
     // carry through the whole kernel.  What the frames of one chunk add up to is wave-uniform
@@ -1123,6 +1277,11 @@ void beam_kernel(BeamArgs a) {
     //      change no prefix and no order, and a run of them costs a few additions ----------
     uint32_t blank_only;  // bit l: blank is the only survivor of frame 32c + l
     int lp_bits;          // lane l: that frame's blank log-prob (fp32 bits)
+    uint64_t light_mask = 0;  // bit l: frame 32c + l is a light one ...
+    uint32_t h_desc = 0;      // ... lane l: its non-blank survivors (3 bits), whether blank survived (bit 3),
+                              // extensions per thread (3 bits), blank-only frames behind it (from bit 8)
+    int h_top = 0;            // lane l: its largest log-prob (fp32 bits) ...
+    int h_run = 0;            // ... and the sum of the blank-only frames' behind it, about
     {
         const int fl = c * kChunk + (lane & (kChunk - 1));
         const HdrHead hh = FLTOP_RING_HEAD(fl);
@@ -1131,6 +1290,22 @@ void beam_kernel(BeamArgs a) {
             inside && hh.count == 1 && hh.s0.tok == 0 && hh.s0.lp > -INFINITY;
         blank_only = (uint32_t)__ballot(lone_blank);
         lp_bits = __float_as_int(hh.s0.lp);
+        if constexpr (kLight) {
+            const int with_blank = hh.s0.tok == 0 ? 1 : 0;
+            const int others = hh.count - with_blank;
+            const int run_behind =
+                lane + 1 < kChunk ? __builtin_ctz(~(blank_only >> (lane + 1)) | 0x80000000u) : 0;
+            int rounds = light_blocks > 0 ? 1 : kLightRounds + 1;
+            while (rounds <= kLightRounds && rounds * light_blocks < others) ++rounds;
+            h_desc = (uint32_t)(others & 7) | (uint32_t)(with_blank << 3) | (uint32_t)(rounds << 4) |
+                     (uint32_t)(run_behind << 8);
+            h_top = __float_as_int(hh.top);
+            const float upto = row32_inclusive_sum(lone_blank ? hh.s0.lp : 0.0f);
+            h_run = __float_as_int(
+                __int_as_float(__builtin_amdgcn_ds_bpermute((lane + run_behind) << 2, __float_as_int(upto))) - upto);
+            light_mask = __ballot(inside && hh.count <= kRegK && others >= 1 && rounds <= kLightRounds &&
+                                  fabsf(hh.top) < INFINITY);
+        }
         const int chunk_survivors = __builtin_amdgcn_readlane(
             wave_inclusive_scan(inside ? hh.count : 0), kWave - 1);
         // records the chunk's frames take beyond the survivors in their headers
@@ -1177,6 +1352,40 @@ void beam_kernel(BeamArgs a) {
             PHASE_MARK(7);
             continue;
         }
+        if constexpr (kLight) {
+            if ((light_mask >> l) & 1ull) {
+                if (links_are == kLinksBuilt) {
+                    // the general path came before: its lists go; no parent is among fresh prefixes
+                    for (int i = tid; i < kHashSlots; i += kThreads) links[gen].ht[i] = -1;
+                    if (tid < kMaxBeam) {
+                        links[gen].first_kid[tid] = -1;
+                        links[gen].kidmask[tid] = 0u;
+                        newslot[tid] = tid;
+                    }
+                    for (int i = tid; i < Tables::kFresh; i += kThreads)
+                        light_tables[light_x ^ 1][kLightBins / 2 + i] = 0u;
+                    links_are = kLinksCoded;
+                    light_spread = (float)(kmax_v - kmin_v) + 1.0f;
+                    light_scale = (float)kLightBins * __builtin_amdgcn_rcpf(light_spread + light_margin);
+                    lds_barrier();
+                }
+#include "fltop_beam_light.inc"
+            }
+            if (links_are != kLinksBuilt) {  // the general path looks children up from their parents
+                build_links(&links[gen]);
+                lds_barrier();
+            }
+        }
+        // (local to the frame: as long as light frames run, none of it takes up a register)
+        FrameCtx<MB> fc;
+        fc.dense_lp = dense_lp;
+        fc.s_tok = s_tok;
+        fc.s_lp = s_lp;
+        fc.lm_lds = (LdsFloatPtr)lm_s;
+        fc.lm_glb = a.lm_table;
+        fc.lm_alpha = a.lm_alpha;
+        fc.lm_beta = a.lm_beta;
+        fc.V = V;
         const FrameHdr hd = ring[t % kChunk];  // all 64 bytes in one round trip
         const int K = hd.count;
 
@@ -1595,6 +1804,13 @@ void beam_kernel(BeamArgs a) {
 
     // ---- streaming: leave the beam for the next chunk -----------------------------------
     if (carried) {
+        if constexpr (kLight) {
+            if (links_are != kLinksBuilt) {
+                __syncthreads();
+                build_links(&links[gen]);
+                __syncthreads();
+            }
+        }
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&slab[gen]);
         uint32_t* dst = reinterpret_cast<uint32_t*>(&carried->slab);
         for (int i = tid; i < (int)(sizeof(BeamSlab<MB>) / 4); i += kThreads) dst[i] = src[i];
@@ -1646,12 +1862,13 @@ __global__ __launch_bounds__(kThreadsSmall) void stream_begin_kernel(StreamState
     }
 }
 
-// The search stage's log-sum-exp, element-wise over two arrays (for checking its rounding).
+// The search stage's log-sum-exp, element-wise over two arrays (for checking its rounding): its two
+// forms take turns.
 __global__ __launch_bounds__(256) void log_add_kernel(const double* __restrict__ a,
                                                       const double* __restrict__ b,
                                                       double* __restrict__ out, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        out[i] = lse2(a[i], b[i]);
+        out[i] = (i & 1) ? lse2(a[i], b[i]) : lse2_any(a[i], b[i]);
 }
 
 }  // namespace
@@ -1803,6 +2020,11 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // frame, gains nothing).
     const bool whole_lists = !long_lists && (p.rel_threshold == 0.0f ||
                                              (!large_beam && likely > (double)entry_threads));
+    // Builds with 256 and 128 threads: frames whose survivors fit their header run as light ones.
+    // Where every frame is known to have more (R = 0, and neither vocabulary nor top-N that small),
+    // a build without that path is 8-10% faster (2 utterances x 124 frames, V = 32, beam 58, Top-8:
+    // 577 against 624 us).
+    const bool never_light = p.rel_threshold == 0.0f && kept_at_most > kRegK + 1;
     const bool tiny_state = p.beam <= kBeamTiny && carried == nullptr;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
@@ -1811,7 +2033,7 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     if (!large_beam) {
         const int threads = threads_512 ? kThreadsLarge
                                         : (wide || !dense ? kThreadsSmall : kThreadsDense);
-        a.dcache_rows = dense ? 1 : (wide ? 12 : 8);
+        a.dcache_rows = dense ? (!wide && tiny_state ? 2 : 1) : (wide ? 12 : 8);
         dyn += (size_t)a.dcache_rows * threads * sizeof(uint64_t);
     }
 #define FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, LISTS_)                               \
@@ -1835,9 +2057,13 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
             FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 4, kListsShort);              \
         else if (wide && dense) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamSmall, 4);   \
         else if (wide) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamSmall, 2);            \
+        else if (dense && tiny_state && never_light)                                         \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamTiny, 3, kListsWhole);               \
         else if (dense && tiny_state)                                                        \
             FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamTiny, 3, kListsShort);               \
         else if (dense) FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamSmall, 3, kListsShort);  \
+        else if (never_light)                                                                \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 2, kListsWhole);              \
         else FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 2, kListsShort);             \
     } while (0)
     if (p.lm_table == nullptr)

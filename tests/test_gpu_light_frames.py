@@ -1,0 +1,104 @@
+"""Frames whose survivors fit their header, in the builds with 256 and 128 threads (one thread per
+candidate, or a few candidates per thread): at the beams where the blocks of extensions change size
+(powers of two and their neighbours), for every number of survivors with and without the blank, mixed
+with longer frames and with runs of blank-only ones.  Against the oracle, statistics included."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_09085_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def frames(seed, B, T, V, step=0.0, blank_runs=True):
+    """fp32 [B, T, V]: one to eight tokens per frame within 4 nats of each other, the others at -30."""
+    rng = np.random.default_rng(seed)
+    lp = np.full((B, T, V), -30.0, dtype=np.float64)
+    for b in range(B):
+        for t in range(T):
+            if blank_runs and rng.random() < 0.4:
+                lp[b, t, 0] = -0.1 * rng.random()
+                continue
+            K = min(V, int(rng.integers(1, 9)))
+            # few tokens, so that entries repeat their last one and extend into one another
+            pool = rng.permutation(min(V, 9))
+            if rng.random() < 0.5:
+                pool = np.concatenate(([0], pool[pool != 0]))
+            lp[b, t, pool[:K]] = -4.0 * rng.random(min(K, len(pool)))
+    if step:
+        lp = np.round(lp / step) * step
+    return lp.astype(np.float32)
+
+
+def check(oracle_lib, lp, beam, label, r=0.01, window=0.0, **more):
+    from test_gpu_ties import check_case
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    B, T, _ = lp.shape
+    ln = np.full(B, T, dtype=np.int32)
+    ln[B // 2] = T - T // 3
+    return check_case(torch.device("cuda:0"), oracle_lib, lp, ln, beam, r, 0, window, label, **more)
+
+
+@pytest.mark.parametrize("options", ["plain", "window", "lm"])
+@pytest.mark.parametrize("beam", [1, 2, 7, 16, 17, 32, 33, 63, 64, 65, 85, 86, 127, 128])
+def test_every_block_size(oracle_lib, beam, options):
+    lp = frames(beam, 4, 70, 33)
+    lm = synth.make_bigram_lm(33, seed=beam) if options == "lm" else None
+    check(oracle_lib, lp, beam, f"beam{beam} {options}", window=6.0 if options == "window" else 0.0,
+          lm=lm, lm_weight=0.7, insertion_bonus=0.3)
+
+
+@pytest.mark.parametrize("window", [0.0, 5.0])
+@pytest.mark.parametrize("beam", [1, 15, 32, 33, 64])
+def test_more_utterances_than_the_chip_holds(oracle_lib, beam, window):
+    """The build with 128 threads: two wavefronts, up to three extensions per thread."""
+    B = 2 * torch.cuda.get_device_properties(0).multi_processor_count + 6
+    lp = np.tile(frames(100 + beam, 6, 40, 29), (B // 6 + 1, 1, 1))[:B]
+    check(oracle_lib, np.ascontiguousarray(lp), beam, f"B{B} beam{beam}", window=window)
+
+
+@pytest.mark.parametrize("B", [3, 520])
+@pytest.mark.parametrize("beam", [8, 32, 64])
+def test_equal_scores_are_ordered_by_hash(oracle_lib, beam, B):
+    """Emissions in steps of 1/2: several candidates of one score at the cut, stays and extensions."""
+    lp = np.tile(frames(200 + beam, 3, 40, 12, step=0.5), (B // 3 + 1, 1, 1))[:B]
+    tied, _ = check(oracle_lib, np.ascontiguousarray(lp), beam, f"steps B{B} beam{beam}")
+    assert tied > 0
+
+
+@pytest.mark.parametrize("beam", [3, 20, 50])
+def test_survivors_without_mass_and_far_apart(oracle_lib, beam):
+    """R = 0 on a vocabulary of six: every token survives, also those of log-prob -inf, which are no
+    candidates; some frames lie a million nats below the others, some tokens a thousand below the
+    rest of their frame, so scores leave the bins on either side."""
+    rng = np.random.default_rng(beam)
+    lp = synth.random_emissions(beam, 3, 60, 6, flat=2.0)
+    lp[rng.random(lp.shape) < 0.25] = -np.inf
+    lp[:, :, 0] = np.where(np.isinf(lp).all(axis=2), -0.5, lp[:, :, 0])
+    lp[rng.random(lp.shape) < 0.1] -= 1000.0
+    lp[:, 20] -= 1e6
+    check(oracle_lib, lp.astype(np.float32), beam, f"-inf beam{beam}", r=0.0)
+
+
+@pytest.mark.parametrize("chunk", [1, 7, 32, 33])
+def test_streams_leave_and_enter_light_frames_at_any_chunk(oracle_lib, chunk):
+    """Parents' places and children lists are carried from call to call whichever kind of frame the
+    call ended on."""
+    dev = torch.device("cuda:0")
+    B, T, V, beam = 3, 66, 29, 40
+    lp = frames(300, B, T, V)
+    want_tok, want_sc, _ = oracle_lib.decode(lp, np.full(B, T, dtype=np.int32), beam, 0.01, n_threads=4)
+    live = binding.Stream(B, T, chunk, V, beam, 0.01, dev)
+    live.begin()
+    for t in range(0, T, chunk):
+        n = min(chunk, T - t)
+        piece = np.zeros((B, chunk, V), dtype=np.float32)
+        piece[:, :n] = lp[:, t:t + n]
+        live.feed(torch.from_numpy(piece).to(dev), torch.full((B,), n, dtype=torch.int32, device=dev))
+    torch.cuda.synchronize()
+    lens = live.lengths.cpu().numpy()
+    toks = live.tokens.cpu().numpy()
+    for b in range(B):
+        assert toks[b, :lens[b]].tolist() == want_tok[b], (chunk, b)
+    np.testing.assert_allclose(live.scores.cpu().numpy(), np.asarray(want_sc, dtype=np.float32), atol=1e-4)
