@@ -314,7 +314,9 @@ __device__ __forceinline__ double lse2(double a, double b) {
 // The same from the same series, without branches (an operand may be -inf, or both), with a reciprocal
 // and two Newton steps for the quotient, whose rounding error is carried along as above, and with the
 // coefficients kept in vector registers (40 of them): the compiler's own choice for a polynomial
-// copies every coefficient into the accumulator first.  Taken by light frames.
+// copies every coefficient into the accumulator first.  Taken by light frames and by the builds that
+// leave a thread 256 registers (unpruned V = 1024, beam 64: 11.30 -> 11.16 ms; V = 32, beam 32: 2275 ->
+// 2244 us); in the frames of the builds with fewer it costs 2% (beam 1000: 2257 -> 2309 us).
 __device__ __forceinline__ double fma_regs(double x, double y, double z) {
     double d;
     asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(x), "v"(y), "v"(z));
@@ -371,6 +373,14 @@ __device__ __forceinline__ double lse2_any(double a, double b) {
     tail += upper ? 1.9082149292705877e-10 : 0.0;
     const double body = 2.0 * s + tail;
     return hi + (body + (upper ? 0.6931471803691238 : 0.0));
+}
+
+template <bool REGS>
+__device__ __forceinline__ double lse2_of(double a, double b) {
+    if constexpr (!REGS) return lse2(a, b);
+    if (a == -INFINITY) return b;
+    if (b == -INFINITY) return a;
+    return lse2_any(a, b);
 }
 
 // number of set bits of `mask` below this lane's own position
@@ -1002,6 +1012,7 @@ void beam_kernel(BeamArgs a) {
     // masses (measured: cfg 3 -1.7%); the larger builds, shorter of registers, read it when the
     // entry is copied (measured there: +0.4% to +1.4% otherwise).
     constexpr bool kPrefetchStay = !kEntryMajor;
+    constexpr bool kLseRegs = WAVES == 2;
     // Whether a thread counts all its candidates of the last bin in a register, its stay and first
     // extension included: hundreds of a frame's candidates may lie beyond the histogram's window,
     // and atomics on one word queue up (64 utterances x 500 frames, V = 32, every token kept: 2354
