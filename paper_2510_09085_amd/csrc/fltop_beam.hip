@@ -73,6 +73,10 @@ constexpr int kRegCand = 1;              // extension candidates kept in registe
 // utterances x 500 frames, V = 32, beam 32, every token kept: 2528 / 2279 / 2278 / 2279; 150 frames,
 // beam 100: 1107 / 1113 / 1112 / 1805; 128 x 400, V = 1024, beam 64, R = 0.01: 805 / 781 / 773 / 797).
 constexpr int kFlooredFrom = 4;
+// Tokens that can reach the floor are listed up to this many (1 KB of LDS); beyond it a frame's whole
+// list is gone through.  (128 utterances, V = 1024, every token kept, beam 64: a floor without the list
+// 11.1 ms, with it 2.75 ms: 65 k candidates per frame were scored one by one, now ~1.5 k.)
+constexpr int kListCap = 512;
 constexpr int kChunk = 32;               // frame headers staged per chunk
 constexpr int kWaypoints = 256;
 constexpr uint64_t kGolden = 0x9E3779B97F4A7C15ull;
@@ -592,7 +596,8 @@ __device__ __forceinline__ double lp_of(const FrameCtx<MB>& f, int32_t tok) {
 // What the kernel is built for, as to the survivor lists of the frames it will meet (512 and
 // 1024 threads; see launch_beam): short ones, as a threshold leaves them, every token of a
 // vocabulary that gives a thread up to three candidates, or lists long enough for a score floor.
-enum : int { kListsShort = 0, kListsWhole = 1, kListsLong = 2 };
+// and those whose floor few of the tokens can reach (kListsLongest).
+enum : int { kListsShort = 0, kListsWhole = 1, kListsLong = 2, kListsLongest = 3 };
 
 // The LM flavour is a kernel template parameter: with one kernel serving all three, the
 // LDS read and the global read would meet at a joint wait on both memory counters.
@@ -1005,8 +1010,10 @@ void beam_kernel(BeamArgs a) {
     static_assert(THREADS >= MB, "one thread per beam entry");
     // builds with 512 threads or more take a thread's candidates from one entry (see EntryView)
     constexpr bool kEntryMajor = THREADS >= kThreadsLarge;
-    static_assert(kEntryMajor || LISTS != kListsLong, "the floor is made for the entry-major mapping");
-    constexpr bool FLOOR = LISTS == kListsLong;  // with the score floor (see `floored_frame`)
+    static_assert(kEntryMajor || LISTS < kListsLong, "the floor is made for the entry-major mapping");
+    constexpr bool FLOOR = LISTS >= kListsLong;  // with the score floor (see `floored_frame`)
+    // ... and a list of the tokens that can reach it
+    constexpr bool LISTED = LISTS == kListsLongest;
     static_assert(kEntryMajor || !kColdGlobal, "the largest capacity has no children lists");
     // Builds with four wavefronts read what a staying entry carries over together with its
     // masses (measured: cfg 3 -1.7%); the larger builds, shorter of registers, read it when the
@@ -1052,6 +1059,8 @@ void beam_kernel(BeamArgs a) {
     __shared__ uint64_t sh_floor;  // complement of the largest of the entries' own distances
     __shared__ int32_t sh_toptok;  // non-blank token with the frame's top emission, if there is one
     __shared__ int32_t sh_below;   // candidates below the floor
+    __shared__ uint16_t s_list[LISTED ? kListCap : 2];  // non-blank survivors that can reach it
+    __shared__ int32_t sh_nlist, sh_nout;  // how many those are, and the others with mass
     __shared__ int32_t sh_nnew, sh_blcount, sh_best;
     __shared__ unsigned long long sh_stat[8];
     __shared__ __align__(16) int32_t newslot[kMaxBeam];  // old beam index -> new beam index of an entry that stays
@@ -1143,6 +1152,8 @@ void beam_kernel(BeamArgs a) {
             sh_floor = kAllOnes;
             sh_toptok = INT32_MAX;
             sh_below = 0;
+            sh_nlist = 0;
+            sh_nout = 0;
         }
     }
     if (tid < 8) sh_stat[tid] = 0ull;
@@ -1176,6 +1187,7 @@ void beam_kernel(BeamArgs a) {
         for (int o = kWave / 2; o > 0; o >>= 1) part = fmaxf(part, __shfl_xor(part, o, kWave));
         lm_ub = fmax(0.0, (double)part);
     }
+    const double lm_reach = lm_ub * (1.0 + 0x1p-22);  // the same, whichever way the bound was rounded
     __syncthreads();
     if (kEntryMajor && carried) {  // the pair table is not carried: rebuild it from the links
         if (tid < carried->n_live && links[0].par[tid] >= 0)
@@ -1625,6 +1637,8 @@ void beam_kernel(BeamArgs a) {
                 sh_floor = kAllOnes;
                 sh_toptok = INT32_MAX;
                 sh_below = 0;
+                sh_nlist = 0;
+                sh_nout = 0;
             }
             if (a.frame_beam) a.frame_beam[trace_base + t] = n_new;
         }
@@ -2025,6 +2039,11 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // Long: some thread has kFlooredFrom candidates.
     const bool long_lists =
         kept_at_most > kRegK && likely > (double)((kFlooredFrom - 1) * entry_threads);
+    // A beam of hundreds of entries, one thread each, is spread so far that most tokens of a small
+    // vocabulary can reach its floor (V = 32, beam 1000, R = 0.01: 1506 us with the list of those that
+    // can, 1459 without; beam 512 with a table: 899 against 870; V = 128, beam 1000: 1877 against 1828;
+    // but V = 1024, beam 600: 836 against 1001, and beam 200 gains at V = 32: 1357 against 1414).
+    const bool few_tokens = p.beam > kBeamLarge / 2 && V < 512;
     // Whole: every token is kept, of a vocabulary that gives no thread that many, or a static
     // top-N is filled: up to three candidates per thread, of which most lie beyond the histogram's
     // window (see kCountAll; the 1024-thread build, which gets there with at most six tokens per
@@ -2050,10 +2069,10 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
 #define FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, LISTS_)                               \
     hipLaunchKernelGGL((beam_kernel<LM_, THREADS_, MB_, WAVES_, LISTS_>), dim3((unsigned)B), \
                        dim3(THREADS_), dyn, stream, a)
-#define FLTOP_LAUNCH_SHORT_OR_LONG(LM_, THREADS_, MB_, WAVES_)                        \
-    do {                                                                              \
-        if (long_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsLong);   \
-        else FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsShort);             \
+#define FLTOP_LAUNCH_SHORT_OR_LONG(LM_, THREADS_, MB_, WAVES_)                         \
+    do {                                                                               \
+        if (long_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsLongest); \
+        else FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsShort);              \
     } while (0)
 #define FLTOP_LAUNCH_ANY_LISTS(LM_, THREADS_, MB_, WAVES_)                            \
     do {                                                                              \
@@ -2062,7 +2081,11 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     } while (0)
 #define FLTOP_LAUNCH_BEAM(LM_)                                                               \
     do {                                                                                     \
-        if (huge_beam) FLTOP_LAUNCH_SHORT_OR_LONG(LM_, kThreadsHuge, kBeamHuge, 4);          \
+        if (huge_beam && long_lists && few_tokens)                                           \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsHuge, kBeamHuge, 4, kListsLong);                 \
+        else if (huge_beam) FLTOP_LAUNCH_SHORT_OR_LONG(LM_, kThreadsHuge, kBeamHuge, 4);     \
+        else if (large_beam && long_lists && few_tokens)                                     \
+            FLTOP_LAUNCH_BUILD(LM_, kThreadsLarge, kBeamLarge, 2, kListsLong);               \
         else if (large_beam) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamLarge, 2);      \
         else if (wide && very_dense)                                                         \
             FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 4, kListsShort);              \

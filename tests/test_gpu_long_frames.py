@@ -103,3 +103,27 @@ def test_thresholds_at_which_the_build_changes(oracle_lib, V, beam, top_n, r, si
     lm = synth.make_bigram_lm(V, seed=beam) if with_lm else None
     check_case(torch.device("cuda:0"), oracle_lib, lp, ln, beam, float(np.float32(r * side)), top_n,
                0.0, f"V{V} beam{beam} r{r * side:.5f}", lm=lm, lm_weight=0.6, insertion_bonus=0.2)
+
+
+@pytest.mark.parametrize("options", ["plain", "lm", "window"])
+@pytest.mark.parametrize("beam", [20, 128, 200, 600])
+@pytest.mark.parametrize("near", [1, 300, 511, 512, 513, 1023])
+def test_tokens_that_can_reach_the_floor(oracle_lib, near, beam, options):
+    """`near` tokens lie within a nat of a frame's best, the others 40 nats below: the tokens that can
+    reach the floor are listed up to 512 of them, beyond that the whole list is gone through.  The
+    blank is among either, and a column has no mass."""
+    rng = np.random.default_rng(near + beam)
+    B, T, V = 2, 5, 1026
+    lp = -40.0 - rng.random((B, T, V))
+    for b in range(B):
+        for t in range(T):
+            lp[b, t, rng.permutation(V)[:near]] = -rng.random(near)
+    lp[:, :, 7] = -np.inf
+    more = {}
+    if options == "lm":
+        lm = synth.make_bigram_lm(V, seed=beam)
+        lm[rng.random(lm.shape) < 0.1] = -np.inf
+        more = dict(lm=lm, lm_weight=0.7, insertion_bonus=0.3)
+    from test_gpu_ties import check_case
+    check_case(torch.device("cuda:0"), oracle_lib, lp.astype(np.float32), np.full(B, T, dtype=np.int32),
+               beam, 0.0, 0, 9.0 if options == "window" else 0.0, f"near{near} beam{beam} {options}", **more)
