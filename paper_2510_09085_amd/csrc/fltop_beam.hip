@@ -1328,6 +1328,9 @@ void beam_kernel(BeamArgs a) {
                 __int_as_float(__builtin_amdgcn_ds_bpermute((lane + run_behind) << 2, __float_as_int(upto))) - upto);
             light_mask = __ballot(inside && hh.count <= kRegK && others >= 1 && rounds <= kLightRounds &&
                                   fabsf(hh.top) < INFINITY);
+            // the sums' rounding has to stay below the 1e-3 that `light_slack` adds (and an overflow of
+            // masked rows' log-probs must not get into the bounds): 5 additions of less than 2048 each
+            if (__ballot(!(fabsf(upto) < 1024.0f)) != 0) light_mask = 0;
         }
         const int chunk_survivors = __builtin_amdgcn_readlane(
             wave_inclusive_scan(inside ? hh.count : 0), kWave - 1);

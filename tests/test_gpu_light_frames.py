@@ -102,3 +102,14 @@ def test_streams_leave_and_enter_light_frames_at_any_chunk(oracle_lib, chunk):
     for b in range(B):
         assert toks[b, :lens[b]].tolist() == want_tok[b], (chunk, b)
     np.testing.assert_allclose(live.scores.cpu().numpy(), np.asarray(want_sc, dtype=np.float32), atol=1e-4)
+
+
+@pytest.mark.parametrize("blank", [-1e30, -5e4])
+def test_blank_only_frames_of_masked_rows(oracle_lib, blank):
+    """Rows whose blank has a mask's value and the rest none: in fp32 their sum over a chunk of headers loses
+    what the other frames add, which must not get into the bounds of the scores."""
+    lp = frames(500, 4, 70, 29)
+    for t in (3, 4, 21, 40, 41):
+        lp[:, t] = -np.inf
+        lp[:, t, 0] = blank
+    check(oracle_lib, lp, 40, f"masked {blank}")
