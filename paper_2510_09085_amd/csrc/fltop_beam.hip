@@ -47,6 +47,7 @@
 #include <type_traits>
 
 #include "fltop_internal.h"
+#include "fltop_light.h"
 
 namespace fltop {
 namespace {
@@ -964,7 +965,6 @@ __device__ __forceinline__ void emit_ext_prefetched(const FrameCtx<MB>& f, BeamS
 }
 
 // Light frames (fltop_beam_light.inc).
-constexpr int kLightBins = 256;  // bins of their selection, 16 bits each
 constexpr int kLightRounds = 3;  // most extensions per thread
 typedef unsigned short Ushort2 __attribute__((ext_vector_type(2)));
 // Their tables: the bins, then a bitmap over the hashes of the prefixes that entered.

@@ -1,0 +1,35 @@
+"""The numbers that light frames work with, compiled for the host from the kernel's own header and run
+under UndefinedBehaviorSanitizer (conversions out of an integer's range included): any report fails."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HEAD = """
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include "fltop_light.h"
+using namespace fltop;
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\\n", __LINE__, #c); std::exit(1); } } while (0)
+"""
+
+
+def run(tmp_path, body):
+    source, exe = tmp_path / "numbers.cpp", tmp_path / "numbers"
+    source.write_text(HEAD + "int main() {\n" + body + "\nreturn 0; }\n")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined,float-cast-overflow",
+                    "-fno-sanitize-recover=all", "-I", os.path.join(ROOT, "paper_2510_09085_amd", "csrc"),
+                    str(source), "-o", str(exe)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, done.stdout + done.stderr[-2000:]
+
+
+@pytest.mark.parametrize("x, bin_", [
+    ("INFINITY", 255), ("3.4e38f", 255), ("4294967296.0f", 255), ("256.0f", 255), ("255.9f", 255),
+    ("254.9f", 254), ("1.0f", 1), ("0.99f", 0), ("0.0f", 0), ("-0.5f", 0), ("-7.0f", 0),
+    ("-3.4e38f", 0), ("-INFINITY", 0), ("NAN", 0)])
+def test_every_distance_has_a_bin(tmp_path, x, bin_):
+    """No mass, masked tokens, scores above the reference: inside the table, and defined."""
+    run(tmp_path, f"volatile float x = {x}; CHECK(light_bin(x) == {bin_}u);")
