@@ -1391,7 +1391,7 @@ void beam_kernel(BeamArgs a) {
                     for (int i = tid; i < Tables::kFresh; i += kThreads)
                         light_tables[light_x ^ 1][kLightBins / 2 + i] = 0u;
                     links_are = kLinksCoded;
-                    light_spread = (float)(kmax_v - kmin_v) + 1.0f;
+                    light_spread = light_spread_of((float)(kmax_v - kmin_v) + 1.0f);
                     light_scale = (float)kLightBins * __builtin_amdgcn_rcpf(light_spread + light_margin);
                     lds_barrier();
                 }

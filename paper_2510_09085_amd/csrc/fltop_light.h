@@ -18,6 +18,16 @@ constexpr uint32_t light_bin(float x) {
     return (uint32_t)__builtin_fminf(__builtin_fmaxf(x, 0.0f), (float)(kLightBins - 1));
 }
 
+// What a light frame's bins cover is the spread of the beam's scores and a margin; both the width of a
+// bin and its reciprocal have to stay finite.  The spread at least doubles while the cut lies in the
+// last bin, which masked tokens in the beam can keep up for any number of frames, and a frame without
+// candidates has none.  (1e30 nats in 256 bins: no farther than fp32 reaches by a wide margin, and the
+// frames whose scores lie wider apart find theirs in the last bin.)
+constexpr float kWidestSpread = 1e30f;
+constexpr float light_spread_of(float spread) {
+    return __builtin_fminf(__builtin_fmaxf(spread, 0.0f), kWidestSpread);
+}
+
 }  // namespace fltop
 
 #endif

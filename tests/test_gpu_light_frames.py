@@ -113,3 +113,26 @@ def test_blank_only_frames_of_masked_rows(oracle_lib, blank):
         lp[:, t] = -np.inf
         lp[:, t, 0] = blank
     check(oracle_lib, lp, 40, f"masked {blank}")
+
+
+@pytest.mark.parametrize("mask", [-1e30, -3e38])
+@pytest.mark.parametrize("beam", [40, 64])
+def test_masked_tokens_that_stay_in_the_beam(oracle_lib, beam, mask):
+    """R = 0 on five tokens, three of them masked in every frame: entries lie 1e30 to 1e40 nats below the
+    best for hundreds of light frames, the cut in their last bin."""
+    rng = np.random.default_rng(beam)
+    lp = np.full((3, 90, 5), mask, dtype=np.float32)
+    lp[:, :, 0] = -0.1 - rng.random((3, 90))
+    lp[:, :, 1] = -0.5 - rng.random((3, 90))
+    lp = np.tile(lp, (1, 3, 1))
+    check(oracle_lib, np.ascontiguousarray(lp), beam, f"kept {mask} beam{beam}", r=0.0)
+
+
+@pytest.mark.parametrize("mask", [-1e4, -1e30, -1e36])
+def test_a_table_with_masked_pairs(oracle_lib, mask):
+    """Most pairs of the table masked: prefixes that hold one stay in the beam for want of better ones, in
+    light frames and in longer ones."""
+    lp = frames(600, 3, 90, 12)
+    lm = synth.make_bigram_lm(12, seed=6)
+    lm[np.random.default_rng(7).random(lm.shape) < 0.7] = mask
+    check(oracle_lib, lp, 64, f"table {mask}", lm=lm, lm_weight=0.5, insertion_bonus=1.0)

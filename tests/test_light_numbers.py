@@ -33,3 +33,20 @@ def run(tmp_path, body):
 def test_every_distance_has_a_bin(tmp_path, x, bin_):
     """No mass, masked tokens, scores above the reference: inside the table, and defined."""
     run(tmp_path, f"volatile float x = {x}; CHECK(light_bin(x) == {bin_}u);")
+
+
+@pytest.mark.parametrize("first", ["1.0f", "3.4e38f", "INFINITY", "NAN"])
+def test_bins_stay_finite_however_long_the_cut_lies_in_the_last_one(tmp_path, first):
+    """The recurrence of a light frame whose cut lies in the last row of bins (its spread becomes 512 of
+    them), 2000 times, then one without candidates; `first` is the spread it is entered with."""
+    run(tmp_path, f"""
+    volatile float margin = 1.6f;
+    float spread = light_spread_of({first});
+    for (int frame = 0; frame < 2000; ++frame) {{
+        const float scale = (float)kLightBins * (1.0f / (spread + margin)), width = 1.0f / scale;
+        CHECK(scale > 1.2e-38f && std::isfinite(width));  // (the reciprocal flushes subnormals)
+        CHECK(light_bin((float)1e41 * scale) == 255u && light_bin(-1.0f * scale) == 0u);
+        spread = light_spread_of(width * 512.0f);
+        CHECK(spread >= 0.0f);
+    }}
+    CHECK(light_spread_of((float)-62 * 4.0f) == 0.0f);""")
