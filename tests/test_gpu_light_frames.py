@@ -136,3 +136,57 @@ def test_a_table_with_masked_pairs(oracle_lib, mask):
     lm = synth.make_bigram_lm(12, seed=6)
     lm[np.random.default_rng(7).random(lm.shape) < 0.7] = mask
     check(oracle_lib, lp, 64, f"table {mask}", lm=lm, lm_weight=0.5, insertion_bonus=1.0)
+
+
+@pytest.mark.parametrize("B", [3, 520])
+@pytest.mark.parametrize("beam, tokens", [(8, 6), (16, 3), (32, 5), (64, 6), (64, 4), (100, 3), (128, 3)])
+def test_equal_scores_at_the_cut_few_and_many(beam, tokens, B):
+    """Every token of a frame has the same log-prob, so whole generations of candidates tie at the cut, up to 64
+    of them (which are listed) and more.  The last bit of a log-sum-exp decides there, so it is compared, bit
+    for bit, with the build that has no light frames (which a vocabulary above 64 tokens takes: the same
+    emissions with tokens that never survive)."""
+    dev = torch.device("cuda:0")
+    lp = np.full((3, 150, 12), -30.0, dtype=np.float32)
+    lp[:, :, :tokens] = -1.5
+    lp[:, 60:100] = frames(beam, 3, 40, 12)
+    lp[1, 20:] = frames(beam + 1, 1, 130, 12)[0]
+
+    def decoded(x, **more):
+        ln = torch.full((len(x),), 150, dtype=torch.int32, device=dev)
+        ln[1] = 140
+        return binding.decode(torch.from_numpy(np.ascontiguousarray(x)).to(dev), ln, beam, 0.01, **more)
+
+    want = decoded(np.pad(lp, ((0, 0), (0, 0), (0, 60)), constant_values=-60.0), want_nbest=True)
+    got = decoded(np.tile(lp, (B // 3 + 1, 1, 1))[:B], want_nbest=B == 3)
+    for b in range(3):
+        if b == 1 and B > 3:
+            continue  # (only the first one of its kind is shorter)
+        for key in ("tokens", "lengths", "scores") + (("nbest_count", "nbest_tokens", "nbest_pb", "nbest_pnb")
+                                                      if B == 3 else ()):
+            assert torch.equal(got[key][b], want[key][b]), (key, b)
+    assert torch.equal(got["tokens"][3:B:3], got["tokens"][0].expand_as(got["tokens"][3:B:3]))
+
+
+def test_equal_scores_take_a_bounded_time():
+    """Six equal tokens, beam 64, a cut among hundreds of equal scores: ranked one by one among all candidates
+    that took 25 times as long as frames whose scores differ (12.3 ms for 64 x 200 frames)."""
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(0)
+    equal = np.full((64, 200, 12), -30.0, dtype=np.float32)
+    equal[:, :, :6] = -1.5
+    apart = equal.copy()
+    apart[:, :, :6] -= rng.random((64, 200, 6)).astype(np.float32)
+    ln = torch.full((64,), 200, dtype=torch.int32, device=dev)
+    fastest = []
+    for lp in (equal, apart):
+        x, took = torch.from_numpy(lp).to(dev), []
+        workspace = binding.alloc_workspace(64, 200, 12, 64, dev)
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            binding.decode(x, ln, 64, 0.01, workspace=workspace)
+            end.record()
+            end.synchronize()
+            took.append(start.elapsed_time(end))
+        fastest.append(min(took))
+    assert fastest[0] < 12.0 * fastest[1], fastest  # (measured: 5)
