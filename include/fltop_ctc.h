@@ -273,7 +273,8 @@ int fltop_ctc_token_ranks(const float* logprobs, int32_t B, int32_t T, int32_t V
  * arrays of n values: exposed so that its rounding can be checked against a reference
  * (it is written out for the narrow argument ranges that occur, not taken from the math
  * library: the log1p(exp(.)) term is within 2.5 ulp of its exact value, to which the final
- * addition adds its half ulp). */
+ * addition adds its half ulp).  The kernels hold it in several forms that give the same bits; a
+ * value for which they would not is NaN here. */
 int fltop_ctc_log_add(const double* a, const double* b, double* out, int64_t n,
                       void* hip_stream);
 

@@ -254,106 +254,55 @@ __device__ inline double key_value(uint64_t k) {
 // the argument ranges here are narrow (exp of a non-positive number, log1p of a number in
 // [0,1]), so both are written out for just that: exp by n ln2 + r reduction and the Taylor
 // series to r^13, log1p(u) as log(w) + c/w with w = fl(1+u), c its rounding error, log(w)
-// = k ln2 + 2 atanh(s), s = f/(2+f), series to s^25, the quotient's rounding error carried
-// along.  The term is within 2.4 ulp of the exact one (measured against 80-bit arithmetic
-// on the host), i.e. far below half an ulp of the sum it is added to.
-__device__ __forceinline__ double exp_nonpositive(double x) {
+// = k ln2 + 2 atanh(s), s = f/(2+f), series to s^25.  The quotient is a reciprocal with two
+// Newton steps, times f, its rounding error carried along.  The term is within 2.5 ulp of the
+// exact one (measured against 80-bit arithmetic), i.e. far below half an ulp of the sum it is
+// added to.
+// REGS says only where the series' coefficients are kept; every build of the search rounds alike,
+// so an utterance's scores do not depend on how many others are decoded with it.  In vector
+// registers (40 of them) the multiply-adds read them directly; the compiler's own choice for a
+// polynomial copies every coefficient into the accumulator first.  They are taken by light frames
+// and by the builds that leave a thread 256 registers (unpruned V = 1024, beam 64: 11.30 -> 11.16
+// ms; V = 32, beam 32: 2275 -> 2244 us); in the frames of the builds with fewer they cost 2% (beam
+// 1000: 2257 -> 2309 us).
+template <bool REGS>
+__device__ __forceinline__ double fma_coeff(double x, double y, double coeff) {
+    if constexpr (!REGS) return fma(x, y, coeff);
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(x), "v"(y), "v"(coeff));
+    return d;
+}
+
+// Without branches: an operand may be -inf, or both.
+template <bool REGS>
+__device__ __forceinline__ double lse2_any(double a, double b) {
+    const double hi = fmax(a, b);
+    // exp(-800) is 0, and nothing below gets into the reduction (masses of masked tokens lie up to 1e42
+    // apart, for which n is no integer any more); the difference is NaN for two operands of -inf
+    const double x = fmax(fmin(a, b) - hi, -800.0);
     const double n = rint(x * 1.4426950408889634);  // log2(e)
     // ln2 in two pieces; the upper one has 21 trailing zero bits, so n * upper is exact
     double r = fma(-n, 0.6931471803691238, x);
     r = fma(-n, 1.9082149292705877e-10, r);
     double p = 1.6059043836821613e-10;  // 1/13!, then 1/12! ... 1/2!, 1, 1
-    p = fma(p, r, 2.08767569878681e-09);
-    p = fma(p, r, 2.505210838544172e-08);
-    p = fma(p, r, 2.755731922398589e-07);
-    p = fma(p, r, 2.7557319223985893e-06);
-    p = fma(p, r, 2.48015873015873e-05);
-    p = fma(p, r, 0.0001984126984126984);
-    p = fma(p, r, 0.001388888888888889);
-    p = fma(p, r, 0.008333333333333333);
-    p = fma(p, r, 0.041666666666666664);
-    p = fma(p, r, 0.16666666666666666);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
-    return ldexp(p, (int)n);  // underflows to 0 for very negative x, which is what is wanted
-}
-
-__device__ __forceinline__ double log1p_unit(double u) {  // 0 <= u <= 1
-    const double w = 1.0 + u;
-    const double c = u - (w - 1.0);  // what the addition lost
-    const bool upper = w > 1.4142135623730951;
-    const double f = upper ? fma(w, 0.5, -1.0) : w - 1.0;  // exact; w / 2^k = 1 + f
-    const double den = 2.0 + f;
-    const double s = f / den;
-    const double s_lo = fma(-s, den, f) * __builtin_amdgcn_rcp(den);
-    const double z = s * s;
-    double q = 0.08;  // 2/25, then 2/23 ... 2/3
-    q = fma(q, z, 0.08695652173913043);
-    q = fma(q, z, 0.09523809523809523);
-    q = fma(q, z, 0.10526315789473684);
-    q = fma(q, z, 0.11764705882352941);
-    q = fma(q, z, 0.13333333333333333);
-    q = fma(q, z, 0.15384615384615385);
-    q = fma(q, z, 0.18181818181818182);
-    q = fma(q, z, 0.2222222222222222);
-    q = fma(q, z, 0.2857142857142857);
-    q = fma(q, z, 0.4);
-    q = fma(q, z, 0.6666666666666666);
-    const double cw = (upper ? 0.5 * c : c) * __builtin_amdgcn_rcp(1.0 + f);  // c / w
-    double tail = fma(s * z, q, 2.0 * s_lo + cw);
-    if (upper) tail += 1.9082149292705877e-10;
-    const double body = 2.0 * s + tail;
-    return upper ? 0.6931471803691238 + body : body;
-}
-
-// Skipped by wavefronts in which no lane has two operands.
-__device__ __forceinline__ double lse2(double a, double b) {
-    if (a == -INFINITY) return b;
-    if (b == -INFINITY) return a;
-    const double hi = a > b ? a : b;
-    const double lo = a > b ? b : a;
-    return hi + log1p_unit(exp_nonpositive(lo - hi));
-}
-
-// The same from the same series, without branches (an operand may be -inf, or both), with a reciprocal
-// and two Newton steps for the quotient, whose rounding error is carried along as above, and with the
-// coefficients kept in vector registers (40 of them): the compiler's own choice for a polynomial
-// copies every coefficient into the accumulator first.  Taken by light frames and by the builds that
-// leave a thread 256 registers (unpruned V = 1024, beam 64: 11.30 -> 11.16 ms; V = 32, beam 32: 2275 ->
-// 2244 us); in the frames of the builds with fewer it costs 2% (beam 1000: 2257 -> 2309 us).
-__device__ __forceinline__ double fma_regs(double x, double y, double z) {
-    double d;
-    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(x), "v"(y), "v"(z));
-    return d;
-}
-
-__device__ __forceinline__ double lse2_any(double a, double b) {
-    const double hi = fmax(a, b);
-    const double x = fmax(fmin(a, b) - hi, -800.0);  // (exp(-800) is 0; the difference may be NaN)
-    const double n = rint(x * 1.4426950408889634);
-    double r = fma(-n, 0.6931471803691238, x);
-    r = fma(-n, 1.9082149292705877e-10, r);
-    double p = 1.6059043836821613e-10;
-    p = fma_regs(p, r, 2.08767569878681e-09);
-    p = fma_regs(p, r, 2.505210838544172e-08);
-    p = fma_regs(p, r, 2.755731922398589e-07);
-    p = fma_regs(p, r, 2.7557319223985893e-06);
-    p = fma_regs(p, r, 2.48015873015873e-05);
-    p = fma_regs(p, r, 0.0001984126984126984);
-    p = fma_regs(p, r, 0.001388888888888889);
-    p = fma_regs(p, r, 0.008333333333333333);
-    p = fma_regs(p, r, 0.041666666666666664);
-    p = fma_regs(p, r, 0.16666666666666666);
+    p = fma_coeff<REGS>(p, r, 2.08767569878681e-09);
+    p = fma_coeff<REGS>(p, r, 2.505210838544172e-08);
+    p = fma_coeff<REGS>(p, r, 2.755731922398589e-07);
+    p = fma_coeff<REGS>(p, r, 2.7557319223985893e-06);
+    p = fma_coeff<REGS>(p, r, 2.48015873015873e-05);
+    p = fma_coeff<REGS>(p, r, 0.0001984126984126984);
+    p = fma_coeff<REGS>(p, r, 0.001388888888888889);
+    p = fma_coeff<REGS>(p, r, 0.008333333333333333);
+    p = fma_coeff<REGS>(p, r, 0.041666666666666664);
+    p = fma_coeff<REGS>(p, r, 0.16666666666666666);
     p = fma(p, r, 0.5);
     p = fma(p, r, 1.0);
     p = fma(p, r, 1.0);
     const double u = ldexp(p, (int)n);
     const double w = 1.0 + u;
-    const double c = u - (w - 1.0);
+    const double c = u - (w - 1.0);  // what the addition lost
     const bool upper = w > 1.4142135623730951;
-    const double f = upper ? fma(w, 0.5, -1.0) : w - 1.0;
-    // f / (2 + f): reciprocal, two Newton steps, and the quotient's rounding error carried along
+    const double f = upper ? fma(w, 0.5, -1.0) : w - 1.0;  // exact; w / 2^k = 1 + f
     const double den = 2.0 + f;
     double y = __builtin_amdgcn_rcp(den);
     y = fma(fma(-den, y, 1.0), y, y);
@@ -361,31 +310,36 @@ __device__ __forceinline__ double lse2_any(double a, double b) {
     const double s = f * y;
     const double s_lo = fma(-s, den, f) * y;
     const double z = s * s;
-    double q = 0.08;
-    q = fma_regs(q, z, 0.08695652173913043);
-    q = fma_regs(q, z, 0.09523809523809523);
-    q = fma_regs(q, z, 0.10526315789473684);
-    q = fma_regs(q, z, 0.11764705882352941);
-    q = fma_regs(q, z, 0.13333333333333333);
-    q = fma_regs(q, z, 0.15384615384615385);
-    q = fma_regs(q, z, 0.18181818181818182);
-    q = fma_regs(q, z, 0.2222222222222222);
-    q = fma_regs(q, z, 0.2857142857142857);
-    q = fma_regs(q, z, 0.4);
-    q = fma_regs(q, z, 0.6666666666666666);
-    const double cw = (upper ? 0.5 * c : c) * __builtin_amdgcn_rcp(1.0 + f);
+    double q = 0.08;  // 2/25, then 2/23 ... 2/3
+    q = fma_coeff<REGS>(q, z, 0.08695652173913043);
+    q = fma_coeff<REGS>(q, z, 0.09523809523809523);
+    q = fma_coeff<REGS>(q, z, 0.10526315789473684);
+    q = fma_coeff<REGS>(q, z, 0.11764705882352941);
+    q = fma_coeff<REGS>(q, z, 0.13333333333333333);
+    q = fma_coeff<REGS>(q, z, 0.15384615384615385);
+    q = fma_coeff<REGS>(q, z, 0.18181818181818182);
+    q = fma_coeff<REGS>(q, z, 0.2222222222222222);
+    q = fma_coeff<REGS>(q, z, 0.2857142857142857);
+    q = fma_coeff<REGS>(q, z, 0.4);
+    q = fma_coeff<REGS>(q, z, 0.6666666666666666);
+    const double cw = (upper ? 0.5 * c : c) * __builtin_amdgcn_rcp(1.0 + f);  // c / w
     double tail = fma(s * z, q, 2.0 * s_lo + cw);
+    if constexpr (!REGS) {  // (the same, for builds short of registers)
+        if (upper) tail += 1.9082149292705877e-10;
+        const double body = 2.0 * s + tail;
+        return hi + (upper ? 0.6931471803691238 + body : body);
+    }
     tail += upper ? 1.9082149292705877e-10 : 0.0;
     const double body = 2.0 * s + tail;
     return hi + (body + (upper ? 0.6931471803691238 : 0.0));
 }
 
+// The same, skipped by wavefronts in which no lane has two operands.
 template <bool REGS>
-__device__ __forceinline__ double lse2_of(double a, double b) {
-    if constexpr (!REGS) return lse2(a, b);
+__device__ __forceinline__ double lse2(double a, double b) {
     if (a == -INFINITY) return b;
     if (b == -INFINITY) return a;
-    return lse2_any(a, b);
+    return lse2_any<REGS>(a, b);
 }
 
 // number of set bits of `mask` below this lane's own position
@@ -1890,13 +1844,15 @@ __global__ __launch_bounds__(kThreadsSmall) void stream_begin_kernel(StreamState
     }
 }
 
-// The search stage's log-sum-exp, element-wise over two arrays (for checking its rounding): its two
-// forms take turns.
+// The search stage's log-sum-exp, element-wise over two arrays (for checking its rounding): NaN where
+// the forms that its builds use would not agree in every bit.
 __global__ __launch_bounds__(256) void log_add_kernel(const double* __restrict__ a,
                                                       const double* __restrict__ b,
                                                       double* __restrict__ out, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        out[i] = (i & 1) ? lse2(a[i], b[i]) : lse2_any(a[i], b[i]);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const double x = a[i], y = b[i], r = lse2<false>(x, y);
+        out[i] = lse2_any<false>(x, y) == r && lse2<true>(x, y) == r && lse2_any<true>(x, y) == r ? r : NAN;
+    }
 }
 
 }  // namespace

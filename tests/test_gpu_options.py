@@ -261,7 +261,8 @@ def test_subword_vocabulary_with_global_memory_bigram_table(dev, oracle_lib):
 # --------------------------------------------------------------------------- log-sum-exp
 def test_log_add_against_extended_precision(dev):
     """The search stage's own log-sum-exp against numpy's in 80-bit arithmetic: the term
-    log1p(exp(min - max)) within 2.5 ulp of itself, plus the half ulp of the final addition."""
+    log1p(exp(min - max)) within 2.5 ulp of itself, plus the half ulp of the final addition.  (The call
+    gives NaN where the forms in the kernels' builds would not agree in every bit.)"""
     rng = np.random.default_rng(5)
     n = 200000
     a = -rng.random(n) * 400.0
@@ -274,6 +275,7 @@ def test_log_add_against_extended_precision(dev):
     a[:50] = -np.inf
     b[25:75] = -np.inf
     a[100:110] = b[100:110]  # equal operands: max + ln 2
+    b[110:130] = a[110:130] - np.logspace(3, 42, 20)  # masked tokens: nothing to add
     got = binding.log_add(torch.from_numpy(a).to(dev), torch.from_numpy(b).to(dev)).cpu().numpy()
     with np.errstate(invalid="ignore"):
         ref = np.logaddexp(a.astype(np.longdouble), b.astype(np.longdouble))
@@ -287,6 +289,32 @@ def test_log_add_against_extended_precision(dev):
     assert (err <= bound).all(), float((err / bound).max())
     np.testing.assert_array_equal(got[:25], b[:25])   # -inf is the neutral element
     np.testing.assert_array_equal(got[50:75], a[50:75])
+    np.testing.assert_array_equal(got[110:130], a[110:130])
+    # the same wherever a value stands
+    pairs = [np.repeat(np.concatenate([v, v / 400.0]), 2) for v in (a, b)]
+    twice = binding.log_add(*(torch.from_numpy(v).to(dev) for v in pairs)).cpu().numpy()
+    np.testing.assert_array_equal(twice[0::2], twice[1::2])
     # symmetric in its operands, bit for bit
     back = binding.log_add(torch.from_numpy(b).to(dev), torch.from_numpy(a).to(dev)).cpu().numpy()
     np.testing.assert_array_equal(got, back)
+
+
+@pytest.mark.parametrize("beam", [32, 64, 100])
+def test_masses_do_not_depend_on_the_build(dev, beam):
+    """The final beam's masses in fp64, bit for bit: one utterance alone, in a batch beyond what the chip holds
+    at once (beam <= 64: two wavefronts per utterance), and with a vocabulary above 64 tokens (eight, and
+    four in the larger batch), whose further tokens never survive."""
+    n, T = 20, 14
+    rng = np.random.default_rng(beam)
+    x = np.full((n, T, 12), -30.0)
+    x[:, :, :4] = rng.standard_normal((n, T, 4))  # few prefixes of much mass: sums near zero, where the
+    lp = x - np.logaddexp.reduce(x, axis=2, keepdims=True)  # last bit of a log-sum-exp shows
+    want = None
+    for B, V in ((n, 12), (520, 12), (n, 72), (300, 72), (520, 72)):
+        wide = np.pad(np.tile(lp, (B // n, 1, 1)), ((0, 0), (0, 0), (0, V - 12)), constant_values=-80.0)
+        out = binding.decode(torch.from_numpy(np.ascontiguousarray(wide, dtype=np.float32)).to(dev),
+                             torch.full((B,), T, dtype=torch.int32, device=dev), beam, 0.003, want_nbest=True)
+        got = {k: out[k] for k in ("nbest_count", "nbest_tokens", "nbest_pb", "nbest_pnb")}
+        want = want or {k: v[:n] for k, v in got.items()}
+        for key, v in got.items():
+            assert torch.equal(v.unflatten(0, (B // n, n)), want[key].expand(B // n, *want[key].shape)), (key, B, V)

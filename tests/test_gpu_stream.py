@@ -86,6 +86,22 @@ def test_chunked_decode_equals_whole_decode(dev, oracle_lib, chunk):
     np.testing.assert_array_equal(one["scores"].cpu().numpy(), got["scores"])
 
 
+def test_a_batch_of_streams_equals_its_one_shot_decode(dev):
+    """More streams than the chip holds at once: they keep the 128-entry state, a one-shot decode of beam 32
+    takes the 64-entry build with light frames; scores and tokens are the same all the same."""
+    w = synth.WORKLOADS["cfg2_batch64"]
+    lp, _ = synth.make_emissions(w, utterances=range(8))
+    x = torch.from_numpy(np.ascontiguousarray(np.tile(lp[:, :120], (65, 1, 1)))).to(dev)
+    full = torch.full((520,), 120, dtype=torch.int32, device=dev)
+    one = binding.decode(x, full, w.beam, 0.003)
+    st = binding.Stream(520, 120, 40, w.V, w.beam, 0.003, dev)
+    for t0 in (0, 40, 80):
+        st.feed(x[:, t0:t0 + 40].contiguous(), torch.full_like(full, 40))
+    torch.cuda.synchronize()
+    for key in ("tokens", "lengths", "scores"):
+        assert torch.equal(one[key], getattr(st, key)), key
+
+
 def test_streams_of_different_lengths_with_partial_transcripts(dev, oracle_lib):
     w = synth.WORKLOADS["cfg3_varlen256"]
     all_len = synth.make_lengths(w)
