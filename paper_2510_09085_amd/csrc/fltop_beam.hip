@@ -921,15 +921,22 @@ __device__ __forceinline__ void emit_ext_prefetched(const FrameCtx<MB>& f, BeamS
 // Light frames (fltop_beam_light.inc).
 constexpr int kLightRounds = 3;  // most extensions per thread
 typedef unsigned short Ushort2 __attribute__((ext_vector_type(2)));
-// Their tables: the bins, then a bitmap over the hashes of the prefixes that entered.
-template <int THREADS>
+// Their tables, one per generation: the bins, then a bitmap over the hashes of the prefixes that entered.
+// They take the place of the general path's hash tables, which light frames do not need: with tables of
+// their own (2.5 KB in the 64-entry state) a batch with a table in LDS had 5 workgroups per CU instead
+// of 6 (1536 utterances x 100 frames, V = 32, beam 64, R = 0.001: 816 -> 1169 us).
+template <int THREADS, int MB>
 struct LightTables {
-    static constexpr int kWords = THREADS == kThreadsSmall ? 512 : 256;  // cleared by one store of each thread
+    static constexpr int kWords = SlabTraits<MB>::kHashSlots;
     static constexpr int kFresh = THREADS == kThreadsSmall ? 256 : 128;
     static_assert(kLightBins / 2 + kFresh <= kWords, "bins and bitmap");
     static __device__ __forceinline__ int fresh_word(uint64_t h) {
         return kLightBins / 2 + ((int)((uint32_t)h >> 5) & (kFresh - 1));
     }
+    static __device__ __forceinline__ uint32_t* of(Links<MB>& lk) { return reinterpret_cast<uint32_t*>(lk.ht); }
+    // where, from there, a word per lane lies that nobody reads (light frames have no children lists)
+    static constexpr int kUnread = -(int)((offsetof(Links<MB>, ht) - offsetof(Links<MB>, next_kid)) / 4);
+    static_assert(MB >= kWave, "one per lane");
 };
 
 // Value of another lane, the same one for the whole wavefront.
@@ -1020,10 +1027,7 @@ void beam_kernel(BeamArgs a) {
     __shared__ __align__(16) int32_t newslot[kMaxBeam];  // old beam index -> new beam index of an entry that stays
     // (the builds for more utterances than that have no LDS and registers to spare for them)
     constexpr bool kLight = LISTS == kListsShort && ((THREADS == kThreadsSmall && WAVES == 2) || (THREADS == kThreadsDense && MB == kBeamTiny));
-    using Tables = LightTables<THREADS>;
-    // light frames: bins, bitmap of the prefixes that entered, and a word per lane that nobody reads
-    // (two of each, the idle one is cleared meanwhile)
-    __shared__ __align__(16) uint32_t light_tables[2][kLight ? Tables::kWords + kWave : 4];
+    using Tables = LightTables<THREADS, MB>;
     // light frame in which entry i's extension by non-blank survivor k was last merged, at
     // (k << light_lg) + i
     __shared__ uint32_t light_kill[kLight ? kLightRounds * (kThreads - kWave) : 4];
@@ -1112,7 +1116,6 @@ void beam_kernel(BeamArgs a) {
     }
     if (tid < 8) sh_stat[tid] = 0ull;
     if constexpr (kLight) {
-        for (int i = tid; i < 2 * (Tables::kWords + kWave); i += kThreads) (&light_tables[0][0])[i] = 0u;
         for (int i = tid; i < kLightRounds * (kThreads - kWave); i += kThreads) light_kill[i] = 0u;
     }
     if (carried) {  // the beam as the previous chunk left it
@@ -1194,12 +1197,18 @@ void beam_kernel(BeamArgs a) {
         if (links_are != kLinksCoded) return code;
         if (code >= 0) return newslot[code];
         if (depth == 0 ||
-            ((light_tables[light_x ^ 1][Tables::fresh_word(want)] >> ((uint32_t)want & 31u)) & 1u) == 0)
+            ((Tables::of(links[light_x ^ 1])[Tables::fresh_word(want)] >> ((uint32_t)want & 31u)) & 1u) == 0)
             return -1;
         int p = -1;
         for (int v = 0; v < n_live; ++v)
             if (slab[gen].h[v] == want) p = v;
         return p;
+    };
+    // both generations' tables: empty ones for light frames, empty hash tables for the general path
+    auto fill_tables = [&](int v) {
+        constexpr int kHalf = kThreads / 2;
+        static_assert(!kLight || kHashSlots == 4 * kHalf, "one store of each thread");
+        reinterpret_cast<int4*>(links[tid / kHalf].ht)[tid % kHalf] = make_int4(v, v, v, v);
     };
     // parent places and children lists from what a light frame left
     auto build_links = [&](Links<MB>* lk) {
@@ -1336,14 +1345,12 @@ void beam_kernel(BeamArgs a) {
             if ((light_mask >> l) & 1ull) {
                 if (links_are == kLinksBuilt) {
                     // the general path came before: its lists go; no parent is among fresh prefixes
-                    for (int i = tid; i < kHashSlots; i += kThreads) links[gen].ht[i] = -1;
                     if (tid < kMaxBeam) {
                         links[gen].first_kid[tid] = -1;
                         links[gen].kidmask[tid] = 0u;
                         newslot[tid] = tid;
                     }
-                    for (int i = tid; i < Tables::kFresh; i += kThreads)
-                        light_tables[light_x ^ 1][kLightBins / 2 + i] = 0u;
+                    fill_tables(0);
                     links_are = kLinksCoded;
                     light_spread = light_spread_of((float)(kmax_v - kmin_v) + 1.0f);
                     light_scale = (float)kLightBins * __builtin_amdgcn_rcpf(light_spread + light_margin);
@@ -1354,6 +1361,7 @@ void beam_kernel(BeamArgs a) {
             if (links_are != kLinksBuilt) {  // the general path looks children up from their parents
                 build_links(&links[gen]);
                 lds_barrier();
+                fill_tables(-1);  // its hash tables again (a barrier follows before anything enters them)
             }
         }
         // (local to the frame: as long as light frames run, none of it takes up a register)
