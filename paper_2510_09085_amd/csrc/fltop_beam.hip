@@ -919,7 +919,6 @@ __device__ __forceinline__ void emit_ext_prefetched(const FrameCtx<MB>& f, BeamS
 }
 
 // Light frames (fltop_beam_light.inc).
-constexpr int kLightRounds = 3;  // most extensions per thread
 typedef unsigned short Ushort2 __attribute__((ext_vector_type(2)));
 // Their tables, one per generation: the bins, then a bitmap over the hashes of the prefixes that entered.
 // They take the place of the general path's hash tables, which light frames do not need: with tables of
@@ -1187,9 +1186,10 @@ void beam_kernel(BeamArgs a) {
     // spreads the scores); grows where that was not enough
     float light_margin = (float)light_slack + (has_lm ? 8.0f : 0.5f);
     if constexpr (kLight) {
-        while ((1 << light_lg) < beam) ++light_lg;
-        light_stay_waves = ((1 << light_lg) + kWave - 1) / kWave;
-        light_blocks = (kThreads - light_stay_waves * kWave) >> light_lg;
+        const LightShape shape = light_shape(beam, kThreads);
+        light_lg = shape.lg;
+        light_stay_waves = shape.stay_waves;
+        light_blocks = shape.blocks;
     }
     // place of an entry's parent in the beam (-1: not there)
     auto parent_place = [&](int j, uint64_t want, int32_t depth) -> int {
@@ -1281,8 +1281,7 @@ void beam_kernel(BeamArgs a) {
             const int others = hh.count - with_blank;
             const int run_behind =
                 lane + 1 < kChunk ? __builtin_ctz(~(blank_only >> (lane + 1)) | 0x80000000u) : 0;
-            int rounds = light_blocks > 0 ? 1 : kLightRounds + 1;
-            while (rounds <= kLightRounds && rounds * light_blocks < others) ++rounds;
+            const int rounds = light_rounds(light_blocks, others);
             h_desc = (uint32_t)(others & 7) | (uint32_t)(with_blank << 3) | (uint32_t)(rounds << 4) |
                      (uint32_t)(run_behind << 8);
             h_top = __float_as_int(hh.top);
@@ -2017,12 +2016,14 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // frame, gains nothing).
     const bool whole_lists = !long_lists && (p.rel_threshold == 0.0f ||
                                              (!large_beam && likely > (double)entry_threads));
-    // Builds with 256 and 128 threads: frames whose survivors fit their header run as light ones.
-    // Where every frame is known to have more (R = 0, and neither vocabulary nor top-N that small),
-    // a build without that path is 8-10% faster (2 utterances x 124 frames, V = 32, beam 58, Top-8:
-    // 577 against 624 us).
-    const bool never_light = p.rel_threshold == 0.0f && kept_at_most > kRegK + 1;
     const bool tiny_state = p.beam <= kBeamTiny && carried == nullptr;
+    // Builds with 256 and 128 threads: frames whose survivors fit their header, and whose extensions fit
+    // the threads, run as light ones.  Where no frame can (R = 0: every frame keeps as many), a build
+    // without that path is 4-10% faster (64 utterances x 100 frames, beam 64, Top-7: 560 against 594 us; Top-5,
+    // beam 65, for which three non-blank tokens fit: 492 against 526).
+    const bool never_light =
+        p.rel_threshold == 0.0f &&
+        !light_possible(kept_at_most, p.beam, dense && tiny_state ? kThreadsDense : kThreadsSmall, kRegK);
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
     // threads (frames of up to 6656 candidates are evaluated once) or 16 KB with 256; the

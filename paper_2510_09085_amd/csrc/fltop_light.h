@@ -10,6 +10,32 @@ namespace fltop {
 
 constexpr int kLightBins = 256;  // bins of their selection, 16 bits each
 
+// How a light frame lays its candidates out: wavefronts with the stays, one thread per beam entry, and
+// behind them blocks of 1 << lg threads, each with the beam's extensions by one non-blank survivor, in up to
+// kLightRounds rounds.
+constexpr int kLightRounds = 3;  // most extensions per thread
+struct LightShape {
+    int lg, stay_waves, blocks;
+};
+constexpr LightShape light_shape(int beam, int threads) {
+    LightShape s{0, 1, 0};
+    while ((1 << s.lg) < beam) ++s.lg;
+    s.stay_waves = ((1 << s.lg) + 63) / 64;
+    s.blocks = (threads - s.stay_waves * 64) >> s.lg;
+    return s;
+}
+// Rounds for so many non-blank survivors; more than kLightRounds: not a light frame.
+constexpr int light_rounds(int blocks, int others) {
+    int rounds = blocks > 0 ? 1 : kLightRounds + 1;
+    while (rounds <= kLightRounds && rounds * blocks < others) ++rounds;
+    return rounds;
+}
+// Whether a frame that keeps `kept` tokens can be one (blank may or may not be among them), in a build whose
+// headers hold `inline_survivors`.
+constexpr bool light_possible(int kept, int beam, int threads, int inline_survivors) {
+    return kept <= inline_survivors && light_rounds(light_shape(beam, threads).blocks, kept - 1) <= kLightRounds;
+}
+
 // Bin of a candidate whose score lies `x` bins below the reference.  What has no mass lies infinitely
 // far below, masked tokens farther than any integer counts, and a score may come out a little above
 // the reference: the clamp has to come before the conversion, whose result is undefined outside the

@@ -50,3 +50,20 @@ def test_bins_stay_finite_however_long_the_cut_lies_in_the_last_one(tmp_path, fi
         CHECK(spread >= 0.0f);
     }}
     CHECK(light_spread_of((float)-62 * 4.0f) == 0.0f);""")
+
+
+@pytest.mark.parametrize("threads", [128, 256])
+def test_a_build_without_light_frames_is_taken_only_where_none_can_be_one(tmp_path, threads):
+    """Frames that all keep the same number of tokens (R = 0), against the layout spelled out: threads behind
+    those of the stays, one per beam entry (a power of two) and token, three times over at most."""
+    run(tmp_path, f"""
+    for (int beam = 1; beam <= {threads} / 2; ++beam) {{
+        int size = 1;
+        while (size < beam) size *= 2;
+        const int behind = {threads} - (size <= 64 ? 64 : 128);
+        for (int kept = 2; kept <= 12; ++kept) {{
+            const bool fits = kept <= 6 && 3 * (behind / size) >= kept - 1;
+            CHECK(light_possible(kept, beam, {threads}, 6) == fits);
+        }}
+        CHECK(light_rounds(light_shape(beam, {threads}).blocks, 1) <= kLightRounds);
+    }}""")
