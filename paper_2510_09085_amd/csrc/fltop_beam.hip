@@ -2020,10 +2020,14 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // Builds with 256 and 128 threads: frames whose survivors fit their header, and whose extensions fit
     // the threads, run as light ones.  Where no frame can (R = 0: every frame keeps as many), a build
     // without that path is 4-10% faster (64 utterances x 100 frames, beam 64, Top-7: 560 against 594 us; Top-5,
-    // beam 65, for which three non-blank tokens fit: 492 against 526).
+    // beam 65, for which three non-blank tokens fit: 492 against 526).  Nor does it pay for a stream that
+    // is fed a frame or two per call: what the first and the last frame of a call set up for it costs more
+    // than they gain (64 streams, beam 100, four calls of one frame: 69.1 against 73.5 us, of two 72.0
+    // against 75.2; of five 122.5 against 122.7, and beam 8 103.6 against 95.7).
     const bool never_light =
-        p.rel_threshold == 0.0f &&
-        !light_possible(kept_at_most, p.beam, dense && tiny_state ? kThreadsDense : kThreadsSmall, kRegK);
+        (carried != nullptr && T <= 2) ||
+        (p.rel_threshold == 0.0f &&
+         !light_possible(kept_at_most, p.beam, dense && tiny_state ? kThreadsDense : kThreadsSmall, kRegK));
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
     // threads (frames of up to 6656 candidates are evaluated once) or 16 KB with 256; the
