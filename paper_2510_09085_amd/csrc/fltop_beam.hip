@@ -1136,12 +1136,15 @@ void beam_kernel(BeamArgs a) {
     }
     TrieNode* trie = a.trie + (int64_t)b * trie_stride;
     double lm_ub = 0.0;  // upper bound of any LM term (never below 0)
+    bool lm_gaps = false;  // (uniform) pairs of the table have no mass
     if (has_lm) {
         static_assert(kLmBoundParts == kWave, "one partial maximum per lane");
-        float part = a.lm_bound[lane];
+        const float signed_part = a.lm_bound[lane];
+        if (LISTED) lm_gaps = __builtin_amdgcn_ballot_w64(__float_as_int(signed_part) < 0) != 0;
+        float part = fabsf(signed_part);
 #pragma unroll
         for (int o = kWave / 2; o > 0; o >>= 1) part = fmaxf(part, __shfl_xor(part, o, kWave));
-        lm_ub = fmax(0.0, (double)part);
+        lm_ub = (double)part;
     }
     const double lm_reach = lm_ub * (1.0 + 0x1p-22);  // the same, whichever way the bound was rounded
     __syncthreads();

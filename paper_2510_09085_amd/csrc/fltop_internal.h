@@ -73,7 +73,8 @@ constexpr size_t kColdBytesPerGeneration = (size_t)FLTOP_MAX_BEAM * 20;
 struct Workspace {
     FrameHdr* hdr;      // [B*T]
     TrieNode* trie;     // [B][trie_stride]
-    float* lm_bound;    // [kLmBoundParts] partial maxima of lm_weight*table+bonus
+    float* lm_bound;    // [kLmBoundParts] partial maxima of lm_weight*table+bonus (or 0 where that is more),
+                        // negated (-0 too) where pairs of the part have no mass
     unsigned long long* rec_used;  // [kRecArenas] records handed out per slice of the record array
                                    // (cleared before the prune stage runs)
     void* cold;         // [B][2][kColdBytesPerGeneration] when beam > kBeamInLds, else unused

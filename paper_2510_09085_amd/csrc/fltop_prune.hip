@@ -405,21 +405,30 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(
 
 // max over the table of lm_weight * table + bonus: bounds every LM term from above.  One
 // partial maximum per workgroup (kLmBoundParts of them; the search stage takes the max of
-// those), so that a 4 MB table is read by 64 workgroups and not by one.
+// those), so that a 4 MB table is read by 64 workgroups and not by one.  Its sign says whether the part
+// holds pairs without mass.
 __global__ __launch_bounds__(kThreads) void lm_bound_kernel(const float* __restrict__ table,
                                                             int64_t n, float w, float bonus,
                                                             float* __restrict__ out) {
     __shared__ float s_part[kWaves];
-    float m = -INFINITY;
+    __shared__ int s_gaps;  // pairs without mass among them (-inf, or what the product makes of it)
+    if (threadIdx.x == 0) s_gaps = 0;
+    __syncthreads();
+    float m = 0.0f;  // (the bound never lies below 0)
+    bool gaps = false;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kThreads)
-        m = fmaxf(m, fmaf(w, table[i], bonus));
+         i += (int64_t)gridDim.x * kThreads) {
+        const float term = fmaf(w, table[i], bonus);
+        m = fmaxf(m, term);
+        gaps |= !(term > -INFINITY);
+    }
+    if (gaps) s_gaps = 1;
     m = group_max<kWave>(m);
     if ((threadIdx.x & (kWave - 1)) == 0) s_part[threadIdx.x / kWave] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int i = 1; i < kWaves; ++i) m = fmaxf(m, s_part[i]);
-        out[blockIdx.x] = m;
+        out[blockIdx.x] = s_gaps ? -m : m;
     }
 }
 

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2510_09085_amd import synth
+from paper_2510_09085_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -105,13 +105,14 @@ def test_thresholds_at_which_the_build_changes(oracle_lib, V, beam, top_n, r, si
                0.0, f"V{V} beam{beam} r{r * side:.5f}", lm=lm, lm_weight=0.6, insertion_bonus=0.2)
 
 
-@pytest.mark.parametrize("options", ["plain", "lm", "window"])
+@pytest.mark.parametrize("options", ["plain", "lm", "lm with gaps", "window"])
 @pytest.mark.parametrize("beam", [20, 128, 200, 600])
 @pytest.mark.parametrize("near", [1, 300, 511, 512, 513, 1023])
 def test_tokens_that_can_reach_the_floor(oracle_lib, near, beam, options):
     """`near` tokens lie within a nat of a frame's best, the others 40 nats below: the tokens that can
-    reach the floor are listed up to 512 of them, beyond that the whole list is gone through.  The
-    blank is among either, and a column has no mass."""
+    reach the floor are listed up to 512 of them, beyond that the whole list is gone through, and also
+    where the statistics are asked for and pairs of the table have no mass.  The blank is among either,
+    and a column has no mass."""
     rng = np.random.default_rng(near + beam)
     B, T, V = 2, 5, 1026
     lp = -40.0 - rng.random((B, T, V))
@@ -120,10 +121,28 @@ def test_tokens_that_can_reach_the_floor(oracle_lib, near, beam, options):
             lp[b, t, rng.permutation(V)[:near]] = -rng.random(near)
     lp[:, :, 7] = -np.inf
     more = {}
-    if options == "lm":
+    if options.startswith("lm"):
         lm = synth.make_bigram_lm(V, seed=beam)
-        lm[rng.random(lm.shape) < 0.1] = -np.inf
+        if options == "lm with gaps":
+            lm[rng.random(lm.shape) < 0.1] = -np.inf
         more = dict(lm=lm, lm_weight=0.7, insertion_bonus=0.3)
     from test_gpu_ties import check_case
     check_case(torch.device("cuda:0"), oracle_lib, lp.astype(np.float32), np.full(B, T, dtype=np.int32),
                beam, 0.0, 0, 9.0 if options == "window" else 0.0, f"near{near} beam{beam} {options}", **more)
+    if options == "lm with gaps":  # the same without statistics, which lists tokens here too
+        x, ln = torch.from_numpy(lp.astype(np.float32)).to("cuda:0"), torch.full((B,), T, dtype=torch.int32).to("cuda:0")
+        kw = dict(lm_table=torch.from_numpy(lm).to("cuda:0"), lm_weight=0.7, insertion_bonus=0.3, want_nbest=True)
+        with_stats, without = (binding.decode(x, ln, beam, 0.0, want_stats=asked, **kw) for asked in (True, False))
+        for key in ("tokens", "lengths", "scores", "nbest_count", "nbest_tokens", "nbest_pb", "nbest_pnb"):
+            assert torch.equal(with_stats[key], without[key]), key
+
+
+def test_statistics_cost_little_with_a_table(oracle_lib):
+    """Tokens that cannot reach the floor are counted, not scored, for the statistics as well: scored for them,
+    pair by pair, an unpruned search with a table took up to twice as long."""
+    from test_gpu_light_frames import fastest_ms
+    lp = np.tile(synth.random_emissions(5, 4, 30, 1024, flat=3.0), (16, 1, 1)).astype(np.float32)
+    lp[:, :, 1:4] += 4.0
+    table = {"lm_table": torch.from_numpy(synth.make_bigram_lm(1024)).to("cuda:0"), "lm_weight": 0.5}
+    took = [fastest_ms(lp, 64, 0.0, want_stats=asked, **table) for asked in (True, False)]
+    assert took[0] < 1.15 * took[1], took  # (measured: 1.01; scored pair by pair 1.32)
