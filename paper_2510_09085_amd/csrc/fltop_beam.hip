@@ -2041,51 +2041,58 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
         a.dcache_rows = dense ? (!wide && tiny_state ? 2 : 1) : (wide ? 12 : 8);
         dyn += (size_t)a.dcache_rows * threads * sizeof(uint64_t);
     }
-#define FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, LISTS_)                               \
-    hipLaunchKernelGGL((beam_kernel<LM_, THREADS_, MB_, WAVES_, LISTS_>), dim3((unsigned)B), \
+    // (A table that does not fit the LDS has more than 64 tokens, which makes a search wide: the builds
+    // for others are not made for it.)
+    auto launch = [&](auto lm_tag) -> hipError_t {
+        constexpr int LM = decltype(lm_tag)::value;
+#define FLTOP_LAUNCH_BUILD(THREADS_, MB_, WAVES_, LISTS_)                                   \
+    hipLaunchKernelGGL((beam_kernel<LM, THREADS_, MB_, WAVES_, LISTS_>), dim3((unsigned)B), \
                        dim3(THREADS_), dyn, stream, a)
-#define FLTOP_LAUNCH_SHORT_OR_LONG(LM_, THREADS_, MB_, WAVES_)                         \
-    do {                                                                               \
-        if (long_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsLongest); \
-        else FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsShort);              \
+#define FLTOP_LAUNCH_SHORT_OR_LONG(THREADS_, MB_, WAVES_)                         \
+    do {                                                                          \
+        if (long_lists) FLTOP_LAUNCH_BUILD(THREADS_, MB_, WAVES_, kListsLongest); \
+        else FLTOP_LAUNCH_BUILD(THREADS_, MB_, WAVES_, kListsShort);              \
     } while (0)
-#define FLTOP_LAUNCH_ANY_LISTS(LM_, THREADS_, MB_, WAVES_)                            \
-    do {                                                                              \
-        if (whole_lists) FLTOP_LAUNCH_BUILD(LM_, THREADS_, MB_, WAVES_, kListsWhole); \
-        else FLTOP_LAUNCH_SHORT_OR_LONG(LM_, THREADS_, MB_, WAVES_);                  \
+#define FLTOP_LAUNCH_ANY_LISTS(THREADS_, MB_, WAVES_)                            \
+    do {                                                                         \
+        if (whole_lists) FLTOP_LAUNCH_BUILD(THREADS_, MB_, WAVES_, kListsWhole); \
+        else FLTOP_LAUNCH_SHORT_OR_LONG(THREADS_, MB_, WAVES_);                  \
     } while (0)
-#define FLTOP_LAUNCH_BEAM(LM_)                                                               \
-    do {                                                                                     \
-        if (huge_beam && long_lists && few_tokens)                                           \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsHuge, kBeamHuge, 4, kListsLong);                 \
-        else if (huge_beam) FLTOP_LAUNCH_SHORT_OR_LONG(LM_, kThreadsHuge, kBeamHuge, 4);     \
-        else if (large_beam && long_lists && few_tokens)                                     \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsLarge, kBeamLarge, 2, kListsLong);               \
-        else if (large_beam) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamLarge, 2);      \
-        else if (wide && very_dense)                                                         \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 4, kListsShort);              \
-        else if (wide && dense) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamSmall, 4);   \
-        else if (wide) FLTOP_LAUNCH_ANY_LISTS(LM_, kThreadsLarge, kBeamSmall, 2);            \
-        else if (dense && tiny_state && never_light)                                         \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamTiny, 3, kListsWhole);               \
-        else if (dense && tiny_state)                                                        \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamTiny, 3, kListsShort);               \
-        else if (dense) FLTOP_LAUNCH_BUILD(LM_, kThreadsDense, kBeamSmall, 3, kListsShort);  \
-        else if (never_light)                                                                \
-            FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 2, kListsWhole);              \
-        else FLTOP_LAUNCH_BUILD(LM_, kThreadsSmall, kBeamSmall, 2, kListsShort);             \
-    } while (0)
-    if (p.lm_table == nullptr)
-        FLTOP_LAUNCH_BEAM(kLmNone);
-    else if (a.lm_in_lds)
-        FLTOP_LAUNCH_BEAM(kLmLds);
-    else
-        FLTOP_LAUNCH_BEAM(kLmGlobal);
-#undef FLTOP_LAUNCH_BEAM
+        if (huge_beam && long_lists && few_tokens) {
+            FLTOP_LAUNCH_BUILD(kThreadsHuge, kBeamHuge, 4, kListsLong);
+        } else if (huge_beam) {
+            FLTOP_LAUNCH_SHORT_OR_LONG(kThreadsHuge, kBeamHuge, 4);
+        } else if (large_beam && long_lists && few_tokens) {
+            FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamLarge, 2, kListsLong);
+        } else if (large_beam) {
+            FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamLarge, 2);
+        } else if (wide && very_dense) {
+            FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 4, kListsShort);
+        } else if (wide && dense) {
+            FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 4);
+        } else if (wide) {
+            FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 2);
+        } else if constexpr (LM == kLmGlobal) {
+            return hipErrorInvalidValue;
+        } else if (dense && tiny_state && never_light) {
+            FLTOP_LAUNCH_BUILD(kThreadsDense, kBeamTiny, 3, kListsWhole);
+        } else if (dense && tiny_state) {
+            FLTOP_LAUNCH_BUILD(kThreadsDense, kBeamTiny, 3, kListsShort);
+        } else if (dense) {
+            FLTOP_LAUNCH_BUILD(kThreadsDense, kBeamSmall, 3, kListsShort);
+        } else if (never_light) {
+            FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsWhole);
+        } else {
+            FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsShort);
+        }
+        return hipGetLastError();
 #undef FLTOP_LAUNCH_ANY_LISTS
 #undef FLTOP_LAUNCH_SHORT_OR_LONG
 #undef FLTOP_LAUNCH_BUILD
-    return hipGetLastError();
+    };
+    if (p.lm_table == nullptr) return launch(std::integral_constant<int, kLmNone>{});
+    if (a.lm_in_lds) return launch(std::integral_constant<int, kLmLds>{});
+    return launch(std::integral_constant<int, kLmGlobal>{});
 }
 
 }  // namespace fltop

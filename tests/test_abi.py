@@ -238,3 +238,12 @@ def test_header_is_plain_c_and_the_struct_layout_matches_the_binding(tmp_path):
         if line:
             name, off = line.split()
             assert getattr(binding.FltopParams, name).offset == int(off), name
+
+
+def test_no_search_build_that_nothing_launches(lib):
+    """A table in global memory means more than 64 tokens (a smaller one fits the LDS), so the builds for small
+    vocabularies (128 threads, and 256 at two wavefronts per SIMD) are not made for it."""
+    built = set(re.findall(rb"beam_kernelILi(\d)ELi(\d+)ELi(\d+)ELi(\d)ELi(\d)EE", open(binding.LIB_PATH, "rb").read()))
+    assert (b"1", b"128", b"64", b"3", b"0") in built  # (the names are found at all)
+    small = {k for k in built if k[1] == b"128" or (k[1] == b"256" and k[3] == b"2")}
+    assert not {k for k in small if k[0] == b"2"}
