@@ -1049,8 +1049,8 @@ void beam_kernel(BeamArgs a) {
     // evaluating the candidate again (row j, this thread's place = its candidate number
     // kRegCand + j).  A thread only ever reads what it wrote itself.
     uint64_t* const dcache = reinterpret_cast<uint64_t*>(dyn_lds + a.dcache_off) + tid;
-    // light frames: scores of the candidates, the stays, then the extensions of each round (at most
-    // 5 / 2 of the threads, which is less than the rows of the distance cache, see launch_beam)
+    // light frames: scores of the candidates, the stays, then the extensions of each round
+    // (light_candidates of them; launch_beam makes the distance cache that large)
     double* const light_score = reinterpret_cast<double*>(dyn_lds + a.dcache_off);
     const int drows = a.dcache_rows;
 
@@ -2038,7 +2038,11 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     if (!large_beam) {
         const int threads = threads_512 ? kThreadsLarge
                                         : (wide || !dense ? kThreadsSmall : kThreadsDense);
-        a.dcache_rows = dense ? (!wide && tiny_state ? 2 : 1) : (wide ? 12 : 8);
+        a.dcache_rows = dense ? 1 : (wide ? 12 : 8);
+        if (!wide && (tiny_state || !dense)) {  // the builds with light frames, whose scores lie there
+            const int light_rows = (light_candidates(p.beam, threads) + threads - 1) / threads;
+            if (a.dcache_rows < light_rows) a.dcache_rows = light_rows;
+        }
         dyn += (size_t)a.dcache_rows * threads * sizeof(uint64_t);
     }
     // (A table that does not fit the LDS has more than 64 tokens, which makes a search wide: the builds

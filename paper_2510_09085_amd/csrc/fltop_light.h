@@ -24,6 +24,11 @@ constexpr LightShape light_shape(int beam, int threads) {
     s.blocks = (threads - s.stay_waves * 64) >> s.lg;
     return s;
 }
+// Places of their scores: the stays', then each round's.
+constexpr int light_candidates(int beam, int threads) {
+    const int stays = light_shape(beam, threads).stay_waves * 64;
+    return stays + kLightRounds * (threads - stays);
+}
 // Rounds for so many non-blank survivors; more than kLightRounds: not a light frame.
 constexpr int light_rounds(int blocks, int others) {
     int rounds = blocks > 0 ? 1 : kLightRounds + 1;

@@ -67,3 +67,15 @@ def test_a_build_without_light_frames_is_taken_only_where_none_can_be_one(tmp_pa
         }}
         CHECK(light_rounds(light_shape(beam, {threads}).blocks, 1) <= kLightRounds);
     }}""")
+
+
+@pytest.mark.parametrize("threads", [128, 256])
+def test_scores_of_every_round_have_a_place(tmp_path, threads):
+    """The last thread's last round, at the index the kernel writes it to."""
+    run(tmp_path, f"""
+    for (int beam = 1; beam <= {threads} / 2; ++beam) {{
+        const LightShape s = light_shape(beam, {threads});
+        const int stays = 64 * s.stay_waves, behind = {threads} - stays;
+        CHECK(beam <= stays && s.blocks << s.lg <= behind);
+        CHECK({threads} - 1 + (kLightRounds - 1) * behind < light_candidates(beam, {threads}));
+    }}""")
