@@ -60,7 +60,7 @@ constexpr int kWave = 64;
 // The beam lives in LDS, so its capacity is a compile-time size: kernels are built for a
 // small one (which keeps several workgroups per CU for large batches) and for the largest.
 constexpr int kBeamSmall = 128;
-constexpr int kBeamTiny = 64;  // one-shot decodes of dense batches (17 KB of LDS)
+constexpr int kBeamTiny = 64;  // one-shot decodes of dense batches (20 KB of LDS)
 constexpr int kBeamLarge = 512;
 constexpr int kBeamHuge = FLTOP_MAX_BEAM;  // 1000-entry beams (paper Sec. 4: beam-size 1000)
 static_assert(kBeamHuge == 1024, "the LDS budget below is worked out for 1024 entries");
@@ -70,9 +70,10 @@ constexpr int kExactCap = 64;
 constexpr int kMaxShift = 54;  // kFine << kMaxShift covers all 64-bit distances
 constexpr int kRegK = kInlineSurvivors;  // survivors kept in registers
 constexpr int kRegCand = 1;              // extension candidates kept in registers per thread
-// Candidates per thread from which a frame gets a score floor (times at 2 / 3 / 4 / 8, us: 64
-// utterances x 500 frames, V = 32, beam 32, every token kept: 2528 / 2279 / 2278 / 2279; 150 frames,
-// beam 100: 1107 / 1113 / 1112 / 1805; 128 x 400, V = 1024, beam 64, R = 0.01: 805 / 781 / 773 / 797).
+// Candidates per thread from which a frame gets a score floor (times at 2 / 3 / 4 / 8, us, with the list of
+// tokens below: 64 utterances x 500 frames, V = 32, beam 32, every token kept: 2358 / 2282 / 2282 / 2284;
+// 150 frames, beam 100: 1030 / 1019 / 1019 / 1801; 128 x 400, V = 1024, beam 64, R = 0.01: 763 / 751 / 752 /
+// 812; 64 x 400, V = 100, beam 32, R = 0.001: 1160 / 1148 / 1156 / 1175).
 constexpr int kFlooredFrom = 4;
 // Tokens that can reach the floor are listed up to this many (1 KB of LDS); beyond it a frame's whole
 // list is gone through.  (128 utterances, V = 1024, every token kept, beam 64: a floor without the list
@@ -988,7 +989,7 @@ void beam_kernel(BeamArgs a) {
     constexpr bool kCountAll = kEntryMajor && LISTS != kListsShort;
     // Where the last bin's count is handed over: inside the block of a thread's later candidates,
     // which the usual frame of a pruned small vocabulary jumps over, or behind it, which is one
-    // more branch for that frame.  It costs the 256- and 128-thread builds without a table 2-3% (64
+    // more branch for that frame (measured when all of these calls' frames took the general path).  It costs the 256- and 128-thread builds without a table 2-3% (64
     // utterances x 500 frames, V = 32, beam 32: 625 against 644 us; 4096 of them: 2287 against
     // 2327); with a table in LDS they are 0.2-2% faster with it (128 x 500, beam 64: 692 against
     // 690 us; 1500 x 60, beam 100, R = 0.001: 1238 against 1213).  The 256-thread build for batches
@@ -1977,7 +1978,7 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // vocabulary leaves hundreds to thousands of candidates per frame, which eight wavefronts
     // (two per SIMD) evaluate twice as fast (measured: V = 1024 27% faster per decode with 512
     // threads, V = 32 at r = 0.01 6% slower).
-    // Beam capacity: up to 128 entries the beam state takes 30 KB of LDS; beyond, the
+    // Beam capacity: up to 128 entries the beam state takes 31 to 35 KB of LDS; beyond, the
     // 512-entry build (116 KB, one thread per entry, one workgroup per CU) is used, and beyond
     // that the 1024-entry build (1024 threads, 134 KB, part of the state in global memory).
     // Residency: at two wavefronts per SIMD a CU holds two 256-thread workgroups (one of 512
@@ -1986,8 +1987,8 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // wavefronts per utterance (one for the stays, one for the extensions: the other two of
     // the four mostly repeat wave-uniform bookkeeping), with registers cut for three
     // wavefronts per SIMD and, where a one-shot decode's beam allows, the 64-entry state
-    // (17 KB of LDS) so that more workgroups fit a CU.  Measured on B = 4096, V = 32,
-    // beam 32: 287 M frames/s with the four-wavefront build alone, 470 M with its registers
+    // (20 KB of LDS) so that more workgroups fit a CU.  Measured on B = 4096, V = 32,
+    // beam 32, before light frames: 287 M frames/s with the four-wavefront build alone, 470 M with its registers
     // cut for four wavefronts per SIMD, 564 M with two wavefronts per utterance, 679 M with
     // the small state as well.  A streaming decode keeps the 128-entry state throughout (its
     // carried records are laid out for it).
@@ -2008,10 +2009,15 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // Long: some thread has kFlooredFrom candidates.
     const bool long_lists =
         kept_at_most > kRegK && likely > (double)((kFlooredFrom - 1) * entry_threads);
-    // A beam of hundreds of entries, one thread each, is spread so far that most tokens of a small
-    // vocabulary can reach its floor (V = 32, beam 1000, R = 0.01: 1506 us with the list of those that
-    // can, 1459 without; beam 512 with a table: 899 against 870; V = 128, beam 1000: 1877 against 1828;
-    // but V = 1024, beam 600: 836 against 1001, and beam 200 gains at V = 32: 1357 against 1414).
+    // A beam of hundreds of entries, one thread each, is spread so far that most tokens of the smallest
+    // vocabularies can reach its floor, and the pass that lists those costs more than it saves.  The line
+    // is drawn for short utterances (32 x 60 frames, time with the list of the time without, beams 257 /
+    // 512 / 1000: V = 32, R = 0.01 1.02 / 1.02 / 1.04, V = 128 1.03 / 1.05 / 1.04, V = 256 1.02 / 1.04 / 1.01, V = 500
+    // 0.92 / 0.94 / 0.95; R = 0.001: V = 64 1.03 / 1.03 / 1.02, V = 256 0.87 / 0.94 / 0.95).  Longer ones, whose
+    // beam is full for most of their frames, would gain from the list from V = 128 on (300 frames: V = 32,
+    // R = 0.01 1.01 / 1.02 / 1.03, V = 128 0.96 / 1.00 / 1.02, V = 256 0.85 / 0.90 / 0.91; R = 0.001: V = 128 0.71 /
+    // 0.80 / 0.88, V = 256 0.54 / 0.63 / 0.65).  Beams of 129 to 256 have it throughout (V = 29 to 256: 60
+    // frames 0.92 to 1.04, 400 frames 0.84 to 1.00).
     const bool few_tokens = p.beam > kBeamLarge / 2 && V < 512;
     // Whole: every token is kept, of a vocabulary that gives no thread that many, or a static
     // top-N is filled: up to three candidates per thread, of which most lie beyond the histogram's
@@ -2034,7 +2040,8 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
     // threads (frames of up to 6656 candidates are evaluated once) or 16 KB with 256; the
-    // builds for large batches get one row (1-4 KB: up to two candidates per thread).
+    // builds for large batches get one row (1-4 KB: up to two candidates per thread), or as many as light
+    // frames need.
     if (!large_beam) {
         const int threads = threads_512 ? kThreadsLarge
                                         : (wide || !dense ? kThreadsSmall : kThreadsDense);
