@@ -43,6 +43,7 @@
 // candidate mapping where frames hold hundreds to thousands of candidates, and two with a
 // tighter register budget for batches that fill the chip, where instruction issue and
 // residency count instead of one frame's latency (see launch_beam).
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -170,6 +171,22 @@ struct alignas(16) Links {
                                              // entered in this generation's frame, keyed by prefix hash
 };
 
+// One beam generation (both parts of it at one offset from the other generation's).
+template <int MB>
+struct Generation {
+    BeamSlab<MB> slab;
+    Links<MB> links;
+};
+
+// What the last wavefront says of the next light frame, and of the state that the others do not follow.
+struct alignas(16) LightLine {
+    uint32_t what, live;      // see fltop_beam_light.inc; entries of the beam
+    float lpb, scale;         // log-prob of the blank (-inf: pruned); bins per nat
+    double ref, kmax;         // above every candidate's score; above every total
+    float spread, margin;
+    int32_t not_light, next_t;
+};
+
 // What a streaming (chunked) decode carries from one call to the next, per utterance: the
 // beam and its links as they stand after the last frame seen, plus the scalars the frame
 // loop keeps in registers.  The prefix trie lives behind the array of these records.
@@ -177,7 +194,7 @@ template <int MB>
 struct StreamState {
     int32_t frames_done;  // frames decoded so far (= trie frame index of the next one)
     int32_t n_live;
-    int32_t collapsed;
+    int32_t collapsed;    // bit 0: the blank-run flag; bit 1: kmin is a bound
     int32_t out_len;      // length of the transcript as last written
     double kmax, kmin;
     // where the transcript and its entry frames were last written: the record of trie nodes
@@ -209,6 +226,7 @@ struct BeamArgs {
     int32_t lm_in_lds;  // 1: table staged into LDS
     int32_t dcache_off;   // dynamic LDS: byte offset of the distance cache ...
     int32_t dcache_rows;  // ... and its size in rows of one distance per thread (0: none)
+    int32_t light_off;    // dynamic LDS: survivors of light frames
     void* stream;          // streaming decode: array of StreamState<MB> (NULL for a one-shot decode)
     int32_t* out_nodes;    // streaming: [B, t_total] trie node behind each written token
     int32_t t_total;       // streaming: frames the trie and the output rows are sized for
@@ -457,7 +475,7 @@ __host__ __device__ inline size_t lm_lds_offset(int V, bool with_s_lp) {
 struct HdrHead {
     int32_t count;
     uint32_t rec_base;
-    float top;
+    float best;
     uint32_t div_magic;
     Survivor s0, s1;
 };
@@ -554,6 +572,8 @@ __device__ __forceinline__ double lp_of(const FrameCtx<MB>& f, int32_t tok) {
 // vocabulary that gives a thread up to three candidates, or lists long enough for a score floor.
 // and those whose floor few of the tokens can reach (kListsLongest).
 enum : int { kListsShort = 0, kListsWhole = 1, kListsLong = 2, kListsLongest = 3 };
+// ... and, added to that, that most of the frames' tokens cannot reach the beam (fltop_beam_reach.inc)
+constexpr int kReachFlag = 8;
 
 // The LM flavour is a kernel template parameter: with one kernel serving all three, the
 // LDS read and the global read would meet at a joint wait on both memory counters.
@@ -928,7 +948,7 @@ typedef unsigned short Ushort2 __attribute__((ext_vector_type(2)));
 template <int THREADS, int MB>
 struct LightTables {
     static constexpr int kWords = SlabTraits<MB>::kHashSlots;
-    static constexpr int kFresh = THREADS == kThreadsSmall ? 256 : 128;
+    static constexpr int kFresh = THREADS == kThreadsDense ? 128 : 256;
     static_assert(kLightBins / 2 + kFresh <= kWords, "bins and bitmap");
     static __device__ __forceinline__ int fresh_word(uint64_t h) {
         return kLightBins / 2 + ((int)((uint32_t)h >> 5) & (kFresh - 1));
@@ -959,9 +979,10 @@ enum : int { kLinksBuilt = 0, kLinksCoded = 1 };
 // frame some per cent slower) so that more utterances are resident when the batch has more
 // workgroups than the chip can hold at 2.
 // LISTS: the survivor lists it is made for.
-template <int LM, int THREADS, int MB, int WAVES, int LISTS>
+template <int LM, int THREADS, int MB, int WAVES, int LISTS_AND_REACH>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 void beam_kernel(BeamArgs a) {
+    constexpr int LISTS = LISTS_AND_REACH & ~kReachFlag;
     constexpr int kThreads = THREADS;
     constexpr int kWalkers = kThreads < kWaypoints ? kThreads : kWaypoints;  // back-walk batch
     static_assert(THREADS >= 4 * kChunk, "a chunk of headers is staged 16 bytes per thread");
@@ -971,8 +992,8 @@ void beam_kernel(BeamArgs a) {
     static_assert(THREADS >= MB, "one thread per beam entry");
     // builds with 512 threads or more take a thread's candidates from one entry (see EntryView)
     constexpr bool kEntryMajor = THREADS >= kThreadsLarge;
-    static_assert(kEntryMajor || LISTS < kListsLong, "the floor is made for the entry-major mapping");
-    constexpr bool FLOOR = LISTS >= kListsLong;  // with the score floor (see `floored_frame`)
+    // (the floor is made for the entry-major mapping)
+    constexpr bool FLOOR = kEntryMajor && LISTS >= kListsLong;  // with the score floor (see `floored_frame`)
     // ... and a list of the tokens that can reach it
     constexpr bool LISTED = LISTS == kListsLongest;
     static_assert(kEntryMajor || !kColdGlobal, "the largest capacity has no children lists");
@@ -1008,8 +1029,7 @@ void beam_kernel(BeamArgs a) {
 #define FLTOP_USUAL(c) (kEntryMajor ? !!(c) : __builtin_expect(!!(c), 1))
     constexpr int kKidSlots = kEntryMajor ? (kColdGlobal ? 2 * MB : 4 * MB) : 4;
     __shared__ uint32_t kidset2[2][kKidSlots];  // (parent place, token) pairs, per generation
-    __shared__ BeamSlab<MB> slab[2];
-    __shared__ Links<MB> links[2];
+    __shared__ Generation<MB> gens[2];
     __shared__ __align__(16) uint32_t hfine[kFine];
     __shared__ __align__(16) uint32_t hcoarse[kCoarse];
     __shared__ uint64_t bl_D[kExactCap], bl_h[kExactCap];
@@ -1026,11 +1046,18 @@ void beam_kernel(BeamArgs a) {
     __shared__ unsigned long long sh_stat[8];
     __shared__ __align__(16) int32_t newslot[kMaxBeam];  // old beam index -> new beam index of an entry that stays
     // (the builds for more utterances than that have no LDS and registers to spare for them)
-    constexpr bool kLight = LISTS == kListsShort && ((THREADS == kThreadsSmall && WAVES == 2) || (THREADS == kThreadsDense && MB == kBeamTiny));
+    // ... of the tokens that can reach the beam only, however long the lists are (kReach), or of all that frames
+    // with few of them keep
+    constexpr bool kReach = (LISTS_AND_REACH & kReachFlag) != 0;
+    static_assert(!kReach || (WAVES == 2 && MB == kBeamSmall), "LDS and registers to spare");
+    constexpr bool kLight =
+        kReach || (LISTS == kListsShort && !kReach && ((THREADS == kThreadsSmall && WAVES == 2) || (THREADS == kThreadsDense && MB == kBeamTiny)));
     using Tables = LightTables<THREADS, MB>;
     // light frame in which entry i's extension by non-blank survivor k was last merged, at
     // (k << light_lg) + i
-    __shared__ uint32_t light_kill[kLight ? kLightRounds * (kThreads - kWave) : 4];
+    __shared__ uint32_t light_kill[kLight && !kReach ? kLightRounds * (kThreads - kWave) : 4];
+    __shared__ LightLine sh_light[2];
+    __shared__ int32_t sh_left[4];  // pairs without mass, or merged, of tokens left out; frame after frame
     extern __shared__ __align__(16) unsigned char dyn_lds[];
 
     const int tid = threadIdx.x;
@@ -1053,6 +1080,16 @@ void beam_kernel(BeamArgs a) {
     // light frames: scores of the candidates, the stays, then the extensions of each round
     // (light_candidates of them; launch_beam makes the distance cache that large)
     double* const light_score = reinterpret_cast<double*>(dyn_lds + a.dcache_off);
+    // kReach: the survivors of a light frame, for every second frame each: by token (log-prob; the frame's
+    // number in its chunk, and from bit 8 on the token's place in the list, from 1), and listed (one place more
+    // of both: for what is not to be written); and per listed token and entry the light frame in which that
+    // extension was last merged, at (place << light_lg) + entry
+    uint4* const light_tokens = reinterpret_cast<uint4*>(dyn_lds + a.light_off);
+    const int light_table_words = V + 1;  // 16 bytes each
+    const LightShape light_layout = light_shape(beam, kThreads);
+    const int reach_places = reach_list_places(light_layout.blocks, kThreads, V);
+    Survivor* const light_list = reinterpret_cast<Survivor*>(light_tokens + light_table_words);
+    uint32_t* const light_notes = reinterpret_cast<uint32_t*>(light_list + 2 * (reach_places + 1));
     const int drows = a.dcache_rows;
 
     StreamState<MB>* const carried =
@@ -1091,14 +1128,14 @@ void beam_kernel(BeamArgs a) {
         for (int i = tid; i < V * V; i += kThreads) lm_s[i] = a.lm_table[i];
     for (int g2 = 0; g2 < 2; ++g2) {
         if (tid < kMaxBeam) {
-            links[g2].par[tid] = -1;
+            gens[g2].links.par[tid] = -1;
             if (!kColdGlobal) {
-                links[g2].first_kid[tid] = -1;
-                links[g2].next_kid[tid] = -1;
+                gens[g2].links.first_kid[tid] = -1;
+                gens[g2].links.next_kid[tid] = -1;
             }
-            links[g2].kidmask[tid] = 0u;
+            gens[g2].links.kidmask[tid] = 0u;
         }
-        for (int i = tid; i < kHashSlots; i += kThreads) links[g2].ht[i] = -1;
+        for (int i = tid; i < kHashSlots; i += kThreads) gens[g2].links.ht[i] = -1;
     }
     if (kEntryMajor)
         for (int i = tid; i < 2 * kKidSlots; i += kThreads) (&kidset2[0][0])[i] = kNoKid;
@@ -1116,24 +1153,28 @@ void beam_kernel(BeamArgs a) {
     }
     if (tid < 8) sh_stat[tid] = 0ull;
     if constexpr (kLight) {
-        for (int i = tid; i < kLightRounds * (kThreads - kWave); i += kThreads) light_kill[i] = 0u;
+        if constexpr (!kReach) {
+            for (int i = tid; i < kLightRounds * (kThreads - kWave); i += kThreads) light_kill[i] = 0u;
+        } else if (a.light_off != 0) {
+            for (int i = tid; i < reach_places << light_layout.lg; i += kThreads) light_notes[i] = 0u;
+        }
     }
     if (carried) {  // the beam as the previous chunk left it
         __syncthreads();  // the link arrays were just preset by other threads
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&carried->slab);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(&slab[0]);
+        uint32_t* dst = reinterpret_cast<uint32_t*>(&gens[0].slab);
         for (int i = tid; i < (int)(sizeof(BeamSlab<MB>) / 4); i += kThreads) dst[i] = src[i];
         const uint32_t* lsrc = reinterpret_cast<const uint32_t*>(carried->par);
-        uint32_t* ldst = reinterpret_cast<uint32_t*>(&links[0]);
+        uint32_t* ldst = reinterpret_cast<uint32_t*>(&gens[0].links);
         for (int i = tid; i < 4 * kMaxBeam; i += kThreads) ldst[i] = lsrc[i];
     } else if (tid == 0) {
-        BeamSlab<MB>& s0 = slab[0];
+        BeamSlab<MB>& s0 = gens[0].slab;
         s0.h[0] = kGolden;
         s0.pb[0] = 0.0;
         s0.pnb[0] = -INFINITY;
         s0.ptot[0] = 0.0;
         s0.last[0] = -1;
-        ColdRef<MB>{&slab[0], cold_gen}.set(0, 0, 0, 0, 0);
+        ColdRef<MB>{&gens[0].slab, cold_gen}.set(0, 0, 0, 0, 0);
     }
     TrieNode* trie = a.trie + (int64_t)b * trie_stride;
     double lm_ub = 0.0;  // upper bound of any LM term (never below 0)
@@ -1141,7 +1182,7 @@ void beam_kernel(BeamArgs a) {
     if (has_lm) {
         static_assert(kLmBoundParts == kWave, "one partial maximum per lane");
         const float signed_part = a.lm_bound[lane];
-        if (LISTED) lm_gaps = __builtin_amdgcn_ballot_w64(__float_as_int(signed_part) < 0) != 0;
+        if (LISTED || kLight) lm_gaps = __builtin_amdgcn_ballot_w64(__float_as_int(signed_part) < 0) != 0;
         float part = fabsf(signed_part);
 #pragma unroll
         for (int o = kWave / 2; o > 0; o >>= 1) part = fmaxf(part, __shfl_xor(part, o, kWave));
@@ -1150,8 +1191,8 @@ void beam_kernel(BeamArgs a) {
     const double lm_reach = lm_ub * (1.0 + 0x1p-22);  // the same, whichever way the bound was rounded
     __syncthreads();
     if (kEntryMajor && carried) {  // the pair table is not carried: rebuild it from the links
-        if (tid < carried->n_live && links[0].par[tid] >= 0)
-            kidset_insert(kidset2[0], kKidSlots, links[0].par[tid], slab[0].last[tid]);
+        if (tid < carried->n_live && gens[0].links.par[tid] >= 0)
+            kidset_insert(kidset2[0], kKidSlots, gens[0].links.par[tid], gens[0].slab.last[tid]);
         __syncthreads();
     }
 
@@ -1159,10 +1200,11 @@ void beam_kernel(BeamArgs a) {
     const int floored_above = (kFlooredFrom - 1) * (kThreads / beam);
     int mapped_for = -1;  // kEntryMajor: the beam size the thread -> entry mapping was made for
     int ext_i = 0, ext_g = 0, ext_G = 1;
-    int gen = 0;         // beam generation: slab[gen], links[gen]
+    int gen = 0;         // beam generation: gens[gen].slab, gens[gen].links
     int n_live = 1;
     bool collapsed = false;  // blank-only frames since the beam was last written
     double kmax_v = 0.0, kmin_v = 0.0;  // bounds of the best / worst score
+    bool kmin_sure = false;  // the latter is a bound, not an estimate
     bool failed = false;     // a frame's survivor records did not fit the workspace
     int prev_out_len = 0;       // streaming: length of the transcript the last call wrote ...
     uint64_t prev_tokens_at = 0, prev_frames_at = 0;  // ... and the rows it wrote it to
@@ -1171,7 +1213,8 @@ void beam_kernel(BeamArgs a) {
         prev_tokens_at = carried->out_tokens_at;
         prev_frames_at = carried->out_frames_at;
         n_live = carried->n_live;
-        collapsed = carried->collapsed != 0;
+        collapsed = (carried->collapsed & 1) != 0;
+        kmin_sure = (carried->collapsed & 2) != 0;
         kmax_v = carried->kmax;
         kmin_v = carried->kmin;
     }
@@ -1179,13 +1222,21 @@ void beam_kernel(BeamArgs a) {
     // Light frames: wavefronts [0, light_stay_waves) take the entries that stay; behind them sit
     // light_blocks blocks of 1 << light_lg extensions, one block per non-blank survivor and round.
     int links_are = kLinksBuilt;
+    if constexpr (kLight) {
+        if (tid < 4) sh_left[tid] = 0;
+    }
     const int wave_id = __builtin_amdgcn_readfirstlane(tid / kWave);
     const bool windowed = a.beam_window > 0.0;
-    int light_x = 0;         // which of the two histograms and bitmaps this light frame uses
-    uint32_t light_tag = 0;  // number of the light frame
+    // number of the light frame (above what else stands where the notes are)
+    uint32_t light_tag = kReach ? 1u << 24 : 0u;
     int light_lg = 0, light_stay_waves = 1, light_blocks = 0;
-    float light_spread = 0.0f, light_scale = 0.0f;
+    const float light_reach = (float)lm_reach + 0.02f;
+    float light_spread = 0.0f, light_scale = 0.0f;  // (builds with two wavefronts)
+    int light_not = -1;       // frame that turned out not to be one
     const double light_slack = lm_ub + 1.0986122886681098 + 1e-3;
+    // whether tokens that cannot reach the beam may be left out: the statistics ask for the number of their
+    // pairs with mass, which follows from the tokens unless pairs of the table have none
+    const bool light_leaves_out = LM == kLmNone || a.stats == nullptr || !lm_gaps;
     // what the bins cover beyond the spread of the beam: how far the cut may fall in one frame (a table
     // spreads the scores); grows where that was not enough
     float light_margin = (float)light_slack + (has_lm ? 8.0f : 0.5f);
@@ -1197,32 +1248,35 @@ void beam_kernel(BeamArgs a) {
     }
     // place of an entry's parent in the beam (-1: not there)
     auto parent_place = [&](int j, uint64_t want, int32_t depth) -> int {
-        const int32_t code = links[gen].par[j];
+        const int32_t code = gens[gen].links.par[j];
         if (links_are != kLinksCoded) return code;
         if (code >= 0) return newslot[code];
         if (depth == 0 ||
-            ((Tables::of(links[light_x ^ 1])[Tables::fresh_word(want)] >> ((uint32_t)want & 31u)) & 1u) == 0)
+            ((Tables::of(gens[gen ^ 1].links)[Tables::fresh_word(want)] >> ((uint32_t)want & 31u)) & 1u) == 0)
             return -1;
         int p = -1;
         for (int v = 0; v < n_live; ++v)
-            if (slab[gen].h[v] == want) p = v;
+            if (gens[gen].slab.h[v] == want) p = v;
         return p;
     };
     // both generations' tables: empty ones for light frames, empty hash tables for the general path
     auto fill_tables = [&](int v) {
-        constexpr int kHalf = kThreads / 2;
-        static_assert(!kLight || kHashSlots == 4 * kHalf, "one store of each thread");
-        reinterpret_cast<int4*>(links[tid / kHalf].ht)[tid % kHalf] = make_int4(v, v, v, v);
+        constexpr int kHalf = kHashSlots / 4;  // 16 bytes each
+        static_assert(!kLight || 2 * kHalf <= kThreads, "one store of a thread");
+        if (2 * kHalf == kThreads || tid < 2 * kHalf)
+            reinterpret_cast<int4*>(gens[tid / kHalf].links.ht)[tid % kHalf] = make_int4(v, v, v, v);
     };
     // parent places and children lists from what a light frame left
     auto build_links = [&](Links<MB>* lk) {
         if (tid < n_live) {
-            const ColdRef<MB> c{&slab[gen], nullptr};
+            const ColdRef<MB> c{&gens[gen].slab, nullptr};
             const int p = parent_place(tid, c.hp(tid), c.plen(tid));
             lk->par[tid] = p;
             if (p >= 0) {
-                lk->next_kid[tid] = atomicExch(&lk->first_kid[p], tid);
-                atomicOr(&lk->kidmask[p], 1u << (slab[gen].last[tid] & 31));
+                const int32_t tok = gens[gen].slab.last[tid];
+                if (kEntryMajor) kidset_insert(kidset2[gen], kKidSlots, p, tok);
+                else lk->next_kid[tid] = atomicExch(&lk->first_kid[p], tid);
+                atomicOr(&lk->kidmask[p], 1u << (tok & 31));
             }
         }
         links_are = kLinksBuilt;
@@ -1254,11 +1308,16 @@ void beam_kernel(BeamArgs a) {
     uint64_t ph_last = clock64();
 #endif
 
+    int32_t touched = 0;
     const int n_chunks = (len + kChunk - 1) / kChunk;
     for (int c = 0; c < n_chunks; ++c) {
     // ---- chunk boundary: headers of frames [32c, 32c+32) into LDS, next chunk requested --
     lds_barrier();  // nobody still reads the previous chunk's headers
     if (tid < 4 * kChunk) reinterpret_cast<uint4*>(&ring[0])[tid] = staged;
+    if constexpr (kReach) {  // (their entries are marked with the frame's number in its chunk)
+        if (a.light_off != 0)
+            for (int i = tid; i < light_table_words; i += kThreads) light_tokens[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
     lds_barrier();
     FLTOP_LOAD_CHUNK(staged, c + 1);
     const int t_end = min(len, (c + 1) * kChunk);
@@ -1266,12 +1325,16 @@ void beam_kernel(BeamArgs a) {
     // ---- classify the chunk's frames (lane l looks at frame 32c + l): blank-only frames
     //      change no prefix and no order, and a run of them costs a few additions ----------
     uint32_t blank_only;  // bit l: blank is the only survivor of frame 32c + l
-    int lp_bits;          // lane l: that frame's blank log-prob (fp32 bits)
+    int lp_bits;          // lane l: that frame's blank log-prob (fp32 bits), -inf if it was pruned
     uint64_t light_mask = 0;  // bit l: frame 32c + l is a light one ...
-    uint32_t h_desc = 0;      // ... lane l: its non-blank survivors (3 bits), whether blank survived (bit 3),
-                              // extensions per thread (3 bits), blank-only frames behind it (from bit 8)
-    int h_top = 0;            // lane l: its largest log-prob (fp32 bits) ...
-    int h_run = 0;            // ... and the sum of the blank-only frames' behind it, about
+    uint32_t h_desc = 0;      // ... lane l: its survivors (13 bits), whether blank is one (bit 15) and whether
+                              // tokens may be left out (bit 14), blank-only frames behind it (from bit 16)
+    int h_top = 0;            // lane l (fp32 bits): its largest log-prob,
+    int h_run = 0;            // no less than the sum of the blank-only frames' behind it (and 2e-3 more at most),
+    int h_alone = 0;          // the spread of the beam below which no token reaches it,
+    int h_grow = 0;           // how far the best total then rises at most, and with those frames
+    int h_grow_run = 0;
+    uint32_t h_rec = 0;       // and where its records start
     {
         const int fl = c * kChunk + (lane & (kChunk - 1));
         const HdrHead hh = FLTOP_RING_HEAD(fl);
@@ -1279,21 +1342,57 @@ void beam_kernel(BeamArgs a) {
         const bool lone_blank =
             inside && hh.count == 1 && hh.s0.tok == 0 && hh.s0.lp > -INFINITY;
         blank_only = (uint32_t)__ballot(lone_blank);
-        lp_bits = __float_as_int(hh.s0.lp);
-        if constexpr (kLight) {
+        lp_bits = __float_as_int(hh.s0.tok == 0 ? hh.s0.lp : -INFINITY);
+        if constexpr (kLight && !kReach) {
             const int with_blank = hh.s0.tok == 0 ? 1 : 0;
             const int others = hh.count - with_blank;
             const int run_behind =
                 lane + 1 < kChunk ? __builtin_ctz(~(blank_only >> (lane + 1)) | 0x80000000u) : 0;
             const int rounds = light_rounds(light_blocks, others);
+            // non-blank survivors (3 bits), whether blank survived (bit 3), extensions per thread (3 bits),
+            // blank-only frames behind it (from bit 8)
             h_desc = (uint32_t)(others & 7) | (uint32_t)(with_blank << 3) | (uint32_t)(rounds << 4) |
                      (uint32_t)(run_behind << 8);
-            h_top = __float_as_int(hh.top);
+            const float frame_best = frame_top(hh.best, hh.s0);
+            h_top = __float_as_int(frame_best);
             const float upto = row32_inclusive_sum(lone_blank ? hh.s0.lp : 0.0f);
             h_run = __float_as_int(
                 __int_as_float(__builtin_amdgcn_ds_bpermute((lane + run_behind) << 2, __float_as_int(upto))) - upto);
             light_mask = __ballot(inside && hh.count <= kRegK && others >= 1 && rounds <= kLightRounds &&
-                                  fabsf(hh.top) < INFINITY);
+                                  fabsf(frame_best) < INFINITY);
+            // the sums' rounding has to stay below the 1e-3 that `light_slack` adds (and an overflow of
+            // masked rows' log-probs must not get into the bounds): 5 additions of less than 2048 each
+            if (__ballot(!(fabsf(upto) < 1024.0f)) != 0) light_mask = 0;
+        }
+        if constexpr (kReach) {
+            const int with_blank = hh.s0.tok == 0 ? 1 : 0;
+            const int others = hh.count - with_blank;
+            const int run_behind =
+                lane + 1 < kChunk ? __builtin_ctz(~(blank_only >> (lane + 1)) | 0x80000000u) : 0;
+            const float lpb = with_blank ? hh.s0.lp : -INFINITY;
+            const float frame_best = fmaxf(hh.best, lpb);
+            // Every entry stays with at least its total and the blank's log-prob.  The margin of 0.02 is far
+            // above what fp32 loses below 1e4.
+            const bool tame = light_leaves_out && fabsf(frame_best) < 1e4f;
+            // (a frame that is none has no survivors here: they are asked for before its turn comes, and its records
+            // may not be there)
+            const bool light = inside && a.light_off != 0 && others >= 1 && hh.count <= kWave &&
+                               (hh.count <= kRegK || hh.rec_base != kNoRecords) && fabsf(frame_best) < INFINITY;
+            h_desc = (uint32_t)(light ? hh.count : 0) | (uint32_t)(tame ? 1 << 14 : 0) | (uint32_t)(with_blank << 15) |
+                     (uint32_t)(run_behind << 16);
+            h_top = __float_as_int(frame_best);
+            h_rec = hh.rec_base;
+            const float gap = tame && lpb > -INFINITY ? lpb - hh.best - light_reach : -INFINITY;
+            h_alone = __float_as_int(windowed ? fminf(gap, (float)a.beam_window * 0.9999f - 2.1f) : gap);
+            // (an entry's own repeat, and its parent's extension)
+            const float merges = (1.0f + __expf(light_reach)) * __expf(hh.best - lpb) * 1.0001f + 1e-3f;
+            h_grow = __float_as_int(merges);
+            const float upto = row32_inclusive_sum(lone_blank ? hh.s0.lp : 0.0f);
+            const float run_sum =
+                __int_as_float(__builtin_amdgcn_ds_bpermute((lane + run_behind) << 2, __float_as_int(upto))) - upto + 1e-3f;
+            h_run = __float_as_int(run_sum);
+            h_grow_run = __float_as_int(lpb + merges + run_sum);
+            light_mask = __ballot(light);
             // the sums' rounding has to stay below the 1e-3 that `light_slack` adds (and an overflow of
             // masked rows' log-probs must not get into the bounds): 5 additions of less than 2048 each
             if (__ballot(!(fabsf(upto) < 1024.0f)) != 0) light_mask = 0;
@@ -1307,6 +1406,14 @@ void beam_kernel(BeamArgs a) {
         if (stat_thread) {
             atomicAdd(&sh_stat[kStSurv], (unsigned long long)chunk_survivors);
             if (chunk_records) atomicAdd(&sh_stat[kStRecords], (unsigned long long)chunk_records);
+        }
+        if constexpr (kReach) {
+            // the lines of the frames' records are asked for ahead of time (light frames last less than a read from
+            // memory takes; what comes is not used, and waited for in the next chunk)
+            const int part = (tid / kChunk) * 16;  // 128 bytes
+            asm volatile("" ::"v"(touched));
+            if (light_mask != 0 && hh.count <= kWave && hh.count - kRegK > part && hh.rec_base != kNoRecords)
+                touched = *reinterpret_cast<const volatile int32_t*>(&rec_all[(int64_t)hh.rec_base + part]);
         }
         // after a frame whose records did not fit the workspace the utterance is not decoded
         // any further, but its survivors are still counted: the caller learns what to ask for
@@ -1325,7 +1432,7 @@ void beam_kernel(BeamArgs a) {
         if (FLTOP_RARE(run > 0)) {
             // every entry's total takes the run's log-probs one by one, in frame order, as a
             // plain implementation adds them (the owner thread keeps the sum in a register)
-            BeamSlab<MB>* const cur_run = &slab[gen];
+            BeamSlab<MB>* const cur_run = &gens[gen].slab;
             double own = tid < n_live ? cur_run->ptot[tid] : 0.0;
             for (int k = 0; k < run; ++k) {
                 const double x = (double)__int_as_float(__builtin_amdgcn_readlane(lp_bits, l + k));
@@ -1345,24 +1452,30 @@ void beam_kernel(BeamArgs a) {
             continue;
         }
         if constexpr (kLight) {
-            if ((light_mask >> l) & 1ull) {
-                if (links_are == kLinksBuilt) {
-                    // the general path came before: its lists go; no parent is among fresh prefixes
-                    if (tid < kMaxBeam) {
-                        links[gen].first_kid[tid] = -1;
-                        links[gen].kidmask[tid] = 0u;
-                        newslot[tid] = tid;
-                    }
-                    fill_tables(0);
-                    links_are = kLinksCoded;
-                    light_spread = light_spread_of((float)(kmax_v - kmin_v) + 1.0f);
-                    light_scale = (float)kLightBins * __builtin_amdgcn_rcpf(light_spread + light_margin);
-                    lds_barrier();
+            if constexpr (kReach) {
+                if (((light_mask >> l) & 1ull) && t != light_not) {
+#include "fltop_beam_reach.inc"
                 }
+            } else {
+                if ((light_mask >> l) & 1ull) {
+                    if (links_are == kLinksBuilt) {
+                        // the general path came before: its lists go; no parent is among fresh prefixes
+                        if (tid < kMaxBeam) {
+                            gens[gen].links.first_kid[tid] = -1;
+                            gens[gen].links.kidmask[tid] = 0u;
+                            newslot[tid] = tid;
+                        }
+                        fill_tables(0);
+                        links_are = kLinksCoded;
+                        light_spread = light_spread_of((float)(kmax_v - kmin_v) + 1.0f);
+                        light_scale = (float)kLightBins * __builtin_amdgcn_rcpf(light_spread + light_margin);
+                        lds_barrier();
+                    }
 #include "fltop_beam_light.inc"
+                }
             }
             if (links_are != kLinksBuilt) {  // the general path looks children up from their parents
-                build_links(&links[gen]);
+                build_links(&gens[gen].links);
                 lds_barrier();
                 fill_tables(-1);  // its hash tables again (a barrier follows before anything enters them)
             }
@@ -1379,11 +1492,12 @@ void beam_kernel(BeamArgs a) {
         fc.V = V;
         const FrameHdr hd = ring[t % kChunk];  // all 64 bytes in one round trip
         const int K = hd.count;
+        const float top = frame_top(hd.best, hd.first[0]);
 
-        BeamSlab<MB>* const cur = &slab[gen];
-        BeamSlab<MB>* const nxt = &slab[gen ^ 1];
-        Links<MB>* const lk = &links[gen];
-        Links<MB>* const lkn = &links[gen ^ 1];
+        BeamSlab<MB>* const cur = &gens[gen].slab;
+        BeamSlab<MB>* const nxt = &gens[gen ^ 1].slab;
+        Links<MB>* const lk = &gens[gen].links;
+        Links<MB>* const lkn = &gens[gen ^ 1].links;
         const ColdRef<MB> ccur{cur, kColdGlobal ? cold_gen + gen : nullptr};
         const ColdRef<MB> cnxt{nxt, kColdGlobal ? cold_gen + (gen ^ 1) : nullptr};
 
@@ -1438,7 +1552,7 @@ void beam_kernel(BeamArgs a) {
                 s_tok[k] = (uint16_t)s.tok;
                 if (kEntryMajor) {
                     s_lp[k] = s.lp;
-                    if (floored_frame && s.lp == hd.top && s.tok != 0) atomicMin(&sh_toptok, s.tok);
+                    if (floored_frame && s.lp == top && s.tok != 0) atomicMin(&sh_toptok, s.tok);
                 }
                 dense_lp[s.tok] = s.lp;
             }
@@ -1470,7 +1584,7 @@ void beam_kernel(BeamArgs a) {
         uint64_t selD = kAllOnes;  // with selH: keep D < selD or (D == selD and hash <= selH)
         uint64_t kbest_key = 0;    // upper bound of the best candidate's key
         // upper bound of every candidate score -> reference key
-        const double ref = kmax_v + (double)hd.top + lm_ub + 1.0986122886681098 + 1e-3;
+        const double ref = kmax_v + (double)top + lm_ub + 1.0986122886681098 + 1e-3;
         fc.Rk = order_key(ref);
         const uint64_t Rk = fc.Rk;
         if constexpr (FLOOR) {
@@ -1615,8 +1729,8 @@ void beam_kernel(BeamArgs a) {
         if (n_new > 0) {
             kmax_v = key_value(kbest_key);
             // worst kept score: the selection threshold when there was one
-            kmin_v = (selD != kAllOnes && selD <= Rk) ? key_value(Rk - selD)
-                                                      : kmin_v + (double)hd.top - 4.0;
+            kmin_sure = selD != kAllOnes && selD <= Rk;
+            kmin_v = kmin_sure ? key_value(Rk - selD) : kmin_v + (double)top - 4.0;
             if (!(kmin_v <= kmax_v)) kmin_v = kmax_v;
         }
         n_live = n_new;
@@ -1654,8 +1768,8 @@ void beam_kernel(BeamArgs a) {
     __syncthreads();
 
     // ---- best prefix (paper: GetHighestScorePrefix) ----------------------------------
-    BeamSlab<MB>& fin = slab[gen];
-    const ColdRef<MB> cfin{&slab[gen], kColdGlobal ? cold_gen + gen : nullptr};
+    BeamSlab<MB>& fin = gens[gen].slab;
+    const ColdRef<MB> cfin{&gens[gen].slab, kColdGlobal ? cold_gen + gen : nullptr};
     int32_t* wp_node = reinterpret_cast<int32_t*>(hfine);  // the histogram is idle now
     int32_t* wp_depth = wp_node + kWaypoints;
     static_assert(2 * kWaypoints <= kFine, "way-points alias the histogram");
@@ -1800,14 +1914,14 @@ void beam_kernel(BeamArgs a) {
         if constexpr (kLight) {
             if (links_are != kLinksBuilt) {
                 __syncthreads();
-                build_links(&links[gen]);
+                build_links(&gens[gen].links);
                 __syncthreads();
             }
         }
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(&slab[gen]);
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(&gens[gen].slab);
         uint32_t* dst = reinterpret_cast<uint32_t*>(&carried->slab);
         for (int i = tid; i < (int)(sizeof(BeamSlab<MB>) / 4); i += kThreads) dst[i] = src[i];
-        const uint32_t* lsrc = reinterpret_cast<const uint32_t*>(&links[gen]);
+        const uint32_t* lsrc = reinterpret_cast<const uint32_t*>(&gens[gen].links);
         uint32_t* ldst = reinterpret_cast<uint32_t*>(carried->par);
         for (int i = tid; i < 4 * kMaxBeam; i += kThreads) ldst[i] = lsrc[i];
         if (tid == 0) {
@@ -1816,7 +1930,7 @@ void beam_kernel(BeamArgs a) {
             carried->out_tokens_at = (uint64_t)(uintptr_t)out_row;
             carried->out_frames_at = (uint64_t)(uintptr_t)born_row;
             carried->n_live = n_live;
-            carried->collapsed = collapsed ? 1 : 0;
+            carried->collapsed = (collapsed ? 1 : 0) | (kmin_sure ? 2 : 0);
             carried->kmax = kmax_v;
             carried->kmin = kmin_v;
         }
@@ -1956,23 +2070,24 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // match (measured on V = 32: from 512 candidates per frame on, the 512-thread build is
     // 9-41% faster; how many tokens a threshold R > 0 keeps is not known here)
     const int kept_at_most = p.top_n > 0 && p.top_n < V ? p.top_n : V;
+    int n_cu = 0;
+    hipError_t qe = compute_units(&n_cu);
+    if (qe != hipSuccess) return qe;
+    const bool very_dense = (int64_t)B > (int64_t)n_cu * 2;
     const bool wide =
-        V > 64 || (p.rel_threshold == 0.0f && (int64_t)p.beam * kept_at_most >= 512);
+        V > 64 || (very_dense && p.rel_threshold == 0.0f && (int64_t)p.beam * kept_at_most >= 512);
     const bool large_beam = p.beam > kBeamSmall;
     const bool huge_beam = p.beam > kBeamLarge;  // 1024-entry build, 1024 threads, one per CU
     if (huge_beam && (carried != nullptr || V > FLTOP_MAX_VOCAB_WIDE_BEAM))
         return hipErrorInvalidValue;  // the entry points refuse these before they get here
-    int n_cu = 0;
-    hipError_t qe = compute_units(&n_cu);
-    if (qe != hipSuccess) return qe;
     const bool dense = (int64_t)B > (int64_t)n_cu * (wide ? 1 : 2);
-    const bool very_dense = (int64_t)B > (int64_t)n_cu * 2;
     const bool threads_512 = large_beam || (wide && !very_dense);  // as dispatched below
     size_t dyn = lm_lds_offset(V, threads_512);
     if (a.lm_in_lds) dyn += (size_t)V * V * sizeof(float);
     dyn = (dyn + 15) / 16 * 16;
     a.dcache_off = (int32_t)dyn;
     a.dcache_rows = 0;
+    a.light_off = 0;
     // Workgroup size: frames of a small vocabulary have a few dozen candidates, and the cost of
     // a frame is its barriers and its longest wavefront, so four wavefronts are best; a large
     // vocabulary leaves hundreds to thousands of candidates per frame, which eight wavefronts
@@ -2026,6 +2141,7 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     const bool whole_lists = !long_lists && (p.rel_threshold == 0.0f ||
                                              (!large_beam && likely > (double)entry_threads));
     const bool tiny_state = p.beam <= kBeamTiny && carried == nullptr;
+    const bool kept_few = p.rel_threshold > 0.0f || kept_at_most <= kWave;
     // Builds with 256 and 128 threads: frames whose survivors fit their header, and whose extensions fit
     // the threads, run as light ones.  Where no frame can (R = 0: every frame keeps as many), a build
     // without that path is 4-10% faster (64 utterances x 100 frames, beam 64, Top-7: 560 against 594 us; Top-5,
@@ -2035,8 +2151,18 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // against 75.2; of five 122.5 against 122.7, and beam 8 103.6 against 95.7).
     const bool never_light =
         (carried != nullptr && T <= 2) ||
-        (p.rel_threshold == 0.0f &&
-         !light_possible(kept_at_most, p.beam, dense && tiny_state ? kThreadsDense : kThreadsSmall, kRegK));
+        (dense && p.rel_threshold == 0.0f && !light_possible(kept_at_most, p.beam, kThreadsDense, kRegK));
+    // Frames that go through the tokens that can reach the beam only (fltop_beam_reach.inc).  Small vocabularies:
+    // where frames with competing tokens keep more than the six that fit their header, so that most would
+    // take the general path (64 utterances x 500 frames, V = 32, beam 32, R = 0: 2229 -> 848 us; R = 0.01,
+    // where plain light frames do: 384 us against 390, with a table 481 against 535, two utterances fed 25 frames
+    // a call, beam 97, table, window 10: 452 against 557).  Vocabularies above 64 tokens: where frames keep up to 64 (a
+    // lane each), which those that keep every token do not (128 x 400, V = 1024, beam 64, R = 0.01: 769 -> 485 us,
+    // with a table in memory 917 -> 819; R = 0 2721 us without, 2853 with it); the largest
+    // ones leave no LDS for the survivors by token.  Not for streams of a frame or two per call.
+    const bool narrow_reach = !wide && !dense && !never_light && likely > 8.0;
+    const bool wide_reach = V > 64 && !dense && !large_beam && V <= 2048 && kept_few && !(carried != nullptr && T <= 2);
+    const bool any_reach = narrow_reach || wide_reach;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
     // threads (frames of up to 6656 candidates are evaluated once) or 16 KB with 256; the
@@ -2046,11 +2172,20 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
         const int threads = threads_512 ? kThreadsLarge
                                         : (wide || !dense ? kThreadsSmall : kThreadsDense);
         a.dcache_rows = dense ? 1 : (wide ? 12 : 8);
-        if (!wide && (tiny_state || !dense)) {  // the builds with light frames, whose scores lie there
-            const int light_rows = (light_candidates(p.beam, threads) + threads - 1) / threads;
-            if (a.dcache_rows < light_rows) a.dcache_rows = light_rows;
-        }
+        const LightShape shape = light_shape(p.beam, threads);
+        // the builds with light frames, whose scores lie there
+        const bool plain_light = !wide && !narrow_reach && (tiny_state || !dense);
+        const int scores = plain_light ? light_candidates(p.beam, threads)
+                                       : (any_reach ? reach_candidates(p.beam, threads, V) : 0);
+        const int light_rows = (scores + threads - 1) / threads;
+        if (a.dcache_rows < light_rows) a.dcache_rows = light_rows;
         dyn += (size_t)a.dcache_rows * threads * sizeof(uint64_t);
+        if (any_reach) {
+            a.light_off = (int32_t)dyn;
+            const int places = reach_list_places(shape.blocks, threads, V);
+            dyn += ((size_t)V + 1) * 16 + 2 * sizeof(Survivor) * (size_t)(places + 1) +
+                   ((size_t)places << shape.lg) * sizeof(uint32_t);
+        }
     }
     // (A table that does not fit the LDS has more than 64 tokens, which makes a search wide: the builds
     // for others are not made for it.)
@@ -2081,6 +2216,12 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
             FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 4, kListsShort);
         } else if (wide && dense) {
             FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 4);
+        } else if (wide_reach && whole_lists) {
+            FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsWhole | kReachFlag);
+        } else if (wide_reach && long_lists) {
+            FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsLongest | kReachFlag);
+        } else if (wide_reach) {
+            FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsShort | kReachFlag);
         } else if (wide) {
             FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 2);
         } else if constexpr (LM == kLmGlobal) {
@@ -2093,6 +2234,8 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
             FLTOP_LAUNCH_BUILD(kThreadsDense, kBeamSmall, 3, kListsShort);
         } else if (never_light) {
             FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsWhole);
+        } else if (narrow_reach) {
+            FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsShort | kReachFlag);
         } else {
             FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsShort);
         }

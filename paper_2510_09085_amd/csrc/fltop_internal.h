@@ -35,7 +35,8 @@ struct alignas(64) FrameHdr {
     int32_t count;       // |S_t| (0 for frames at or beyond the utterance length)
     uint32_t rec_base;   // count > 6: first record of this frame (survivor 6), or kNoRecords
                          // when the record array was full; unused otherwise
-    float top;           // max_v lp[t][v]
+    float best;          // largest log-prob among the survivors other than the blank, -inf if there is none;
+                         // with the blank's own, if it survived, that is the frame's top emission (frame_top)
     uint32_t div_magic;  // floor((2^32 - 1) / n) + 1 for n = non-blank survivors > 1, else 0:
                          // umulhi(e, div_magic) == e / n for every e < 2^19, and at most one
                          // more than that for any larger e below 2^32
@@ -44,6 +45,11 @@ struct alignas(64) FrameHdr {
                                        // (token 0), if it survived, is first[0].
 };
 static_assert(sizeof(FrameHdr) == 64, "FrameHdr must be one 64-byte line");
+
+// Top emission of a frame (it always survives): `best` or the blank's, which is survivor 0 if it is one.
+__host__ __device__ inline float frame_top(float best, const Survivor& first) {
+    return first.tok == 0 && first.lp > best ? first.lp : best;
+}
 
 // One node of the prefix trie (global memory): a prefix is a chain of nodes.
 // `xup` is the nearest ancestor whose depth is a multiple of 8 (strictly above

@@ -188,12 +188,16 @@ __global__ __launch_bounds__(kThreads) void prune_kernel(
         if (rd >= n_rounds) break;
         const FrameRegs<LPF, ITERS, VEC4>& fr = cur[u];
         // ---- top emission and threshold ------------------------------------------------
-        float m = -INFINITY;
+        float m = -INFINITY, others_best = -INFINITY;  // of all tokens; of those other than the blank
 #pragma unroll
         for (int it = 0; it < ITERS; ++it)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) m = fmaxf(m, fr.x[it][e]);
+            for (int e = 0; e < 4; ++e) {
+                m = fmaxf(m, fr.x[it][e]);
+                others_best = fmaxf(others_best, it + e == 0 && lg == 0 ? -INFINITY : fr.x[it][e]);
+            }
         m = group_max<LPF>(m);
+        others_best = group_max<LPF>(others_best);
         const float thr = m + ln_r;  // one fp32 add
 
         // ---- survivors in ascending token order: rank = survivors before it in the frame.
@@ -340,9 +344,10 @@ __global__ __launch_bounds__(kThreads) void prune_kernel(
             int4 h;
             h.x = total;
             h.y = (int)rec_base;
-            h.z = __float_as_int(m);
+            // (where another token than the blank survives, the best of them does)
+            h.z = __float_as_int(others > 0u ? others_best : -INFINITY);
             h.w = others > 1u ? (int)(0xFFFFFFFFu / others + 1u) : 0;
-            *reinterpret_cast<int4*>(img) = h;  // count, rec_base, top, div_magic
+            *reinterpret_cast<int4*>(img) = h;  // count, rec_base, best, div_magic
         }
         // LDS operations of one wavefront execute in order, so the images are complete
         // for the reads below.  Frames beyond the length get no header: never read, and
@@ -385,13 +390,14 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(
     struct Head {
         int32_t count;
         uint32_t rec_base;
-        float top;
+        float best;
         int32_t pad;
+        Survivor first;
     };
     const Head h = *reinterpret_cast<const Head*>(&hdr[g]);
     if (lane == 0) {
         counts[g] = h.count;
-        if (frame_max) frame_max[g] = h.top;
+        if (frame_max) frame_max[g] = frame_top(h.best, h.first);
     }
     // survivors beyond the sixth sit in the frame's stretch of the record array (if they fitted)
     const Survivor* src = rec + ((int64_t)h.rec_base - kInlineSurvivors);

@@ -1,0 +1,91 @@
+"""Frames that go through the tokens that can reach the beam only: small vocabularies whose frames keep more than
+the six survivors of a header, and vocabularies above 64 tokens (256 and 512 threads).  Against the oracle, statistics
+included: at the beams where the blocks of extensions change size, with lists of one token, of more than one round
+and of more than are taken, with frames that no token changes, masked tokens, gaps in the table, windows, streams
+cut anywhere, and records that did not fit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_09085_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def frames(seed, B, T, V, zipf=0.0):
+    """fp32 [B, T, V] of the workloads' kind, whose competitors come close in every third frame or so."""
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((B, T, V))
+    if zipf:
+        x[:, :, 1:] -= zipf * np.log(np.arange(1, V))
+    for b in range(B):
+        for t in range(T):
+            top = 0 if rng.random() < 0.6 else int(rng.integers(1, min(V, 12)))
+            x[b, t, top] += rng.choice((2.0, 7.0, 11.0))
+            if rng.random() < 0.3:  # a burst of tokens that compete
+                n = int(rng.integers(1, min(V, 30)))
+                x[b, t, rng.permutation(V)[:n]] += rng.uniform(2.0, 8.0)
+    m = x.max(axis=2, keepdims=True)
+    return (x - m - np.log(np.exp(x - m).sum(axis=2, keepdims=True))).astype(np.float32)
+
+
+def check(oracle_lib, lp, beam, label, r, window=0.0, top_n=0, **more):
+    from test_gpu_ties import check_case
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    B, T, _ = lp.shape
+    ln = np.full(B, T, dtype=np.int32)
+    ln[B // 2] = T - T // 3
+    return check_case(torch.device("cuda:0"), oracle_lib, lp, ln, beam, r, top_n, window, label, **more)
+
+
+@pytest.mark.parametrize("options", ["plain", "window", "lm"])
+@pytest.mark.parametrize("beam", [1, 2, 15, 16, 17, 32, 33, 64, 65, 100, 128])
+def test_small_vocabularies_that_keep_every_token(oracle_lib, beam, options):
+    lp = frames(beam, 3, 75, 29)
+    lm = synth.make_bigram_lm(29, seed=beam) if options == "lm" else None
+    check(oracle_lib, lp, beam, f"beam{beam} {options}", 0.0, window=5.0 if options == "window" else 0.0,
+          lm=lm, lm_weight=0.7, insertion_bonus=0.3)
+
+
+@pytest.mark.parametrize("r, top_n", [(0.01, 0), (0.0005, 0), (0.0, 20), (0.0, 64)])
+@pytest.mark.parametrize("V, beam", [(65, 1), (65, 64), (100, 65), (257, 31), (1024, 64), (1024, 128), (2048, 64),
+                                     (2048, 128)])
+def test_large_vocabularies(oracle_lib, V, beam, r, top_n):
+    check(oracle_lib, frames(V + beam, 3, 40, V, zipf=1.1), beam, f"V{V} beam{beam} r{r} N{top_n}", r, top_n=top_n)
+
+
+@pytest.mark.parametrize("V, r", [(29, 0.0), (70, 0.003)])
+def test_masked_tokens_and_gaps_in_the_table(oracle_lib, V, r):
+    """Tokens and pairs without mass: never listed, and not counted by the statistics."""
+    lp = frames(7, 4, 60, V)
+    lp[:, ::3, 3::4] = -np.inf
+    lm = synth.make_bigram_lm(V, seed=3)
+    lm[2::5, 1::3] = -np.inf
+    for table in (None, lm):
+        check(oracle_lib, lp, 40, f"V{V} table{table is not None}", r, lm=table, lm_weight=0.7, insertion_bonus=0.3)
+
+
+@pytest.mark.parametrize("V, r", [(32, 0.0), (90, 0.002)])
+@pytest.mark.parametrize("cut", [1, 3, 7, 32, 50])
+def test_streams_give_what_the_whole_utterance_gives(V, r, cut):
+    dev = torch.device("cuda:0")
+    lp = torch.from_numpy(frames(11, 3, 100, V)).to(dev)
+    want = binding.decode(lp, torch.full((3,), 100, dtype=torch.int32, device=dev), 24, r)
+    live = binding.Stream(3, 100, cut, V, 24, r, dev)
+    for t in range(0, 100, cut):
+        n = min(cut, 100 - t)
+        live.feed(lp[:, t:t + n].contiguous(), torch.full((3,), n, dtype=torch.int32, device=dev))
+    assert torch.equal(live.lengths, want["lengths"]) and torch.equal(live.scores, want["scores"])
+    for b in range(3):
+        n = int(want["lengths"][b])
+        assert torch.equal(live.tokens[b, :n], want["tokens"][b, :n])
+
+
+def test_records_that_did_not_fit_are_not_asked_for():
+    """Survivors of the next full frame are read ahead of its turn: not those of a frame without records."""
+    dev = torch.device("cuda:0")
+    B, T, V, beam = 6, 80, 32, 16
+    lp = torch.from_numpy(frames(5, B, T, V)).to(dev)
+    ln = torch.full((B,), T, dtype=torch.int32, device=dev)
+    small = binding.alloc_workspace(B, T, V, beam, dev, max_records=0)
+    assert int(binding.decode(lp, ln, beam, 0.0005, workspace=small)["lengths"].min()) == -1
