@@ -2075,7 +2075,8 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     if (qe != hipSuccess) return qe;
     const bool very_dense = (int64_t)B > (int64_t)n_cu * 2;
     const bool wide =
-        V > 64 || (very_dense && p.rel_threshold == 0.0f && (int64_t)p.beam * kept_at_most >= 512);
+        V > 64 || ((very_dense || p.lm_table != nullptr || p.beam > kBeamTiny) && p.rel_threshold == 0.0f &&
+                   (int64_t)p.beam * kept_at_most >= 512);
     const bool large_beam = p.beam > kBeamSmall;
     const bool huge_beam = p.beam > kBeamLarge;  // 1024-entry build, 1024 threads, one per CU
     if (huge_beam && (carried != nullptr || V > FLTOP_MAX_VOCAB_WIDE_BEAM))
@@ -2149,9 +2150,6 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // is fed a frame or two per call: what the first and the last frame of a call set up for it costs more
     // than they gain (64 streams, beam 100, four calls of one frame: 69.1 against 73.5 us, of two 72.0
     // against 75.2; of five 122.5 against 122.7, and beam 8 103.6 against 95.7).
-    const bool never_light =
-        (carried != nullptr && T <= 2) ||
-        (dense && p.rel_threshold == 0.0f && !light_possible(kept_at_most, p.beam, kThreadsDense, kRegK));
     // Frames that go through the tokens that can reach the beam only (fltop_beam_reach.inc).  Small vocabularies:
     // where frames with competing tokens keep more than the six that fit their header, so that most would
     // take the general path (64 utterances x 500 frames, V = 32, beam 32, R = 0: 2229 -> 848 us; R = 0.01,
@@ -2159,9 +2157,21 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // a call, beam 97, table, window 10: 452 against 557).  Vocabularies above 64 tokens: where frames keep up to 64 (a
     // lane each), which those that keep every token do not (128 x 400, V = 1024, beam 64, R = 0.01: 769 -> 485 us,
     // with a table in memory 917 -> 819; R = 0 2721 us without, 2853 with it); the largest
-    // ones leave no LDS for the survivors by token.  Not for streams of a frame or two per call.
-    const bool narrow_reach = !wide && !dense && !never_light && likely > 8.0;
-    const bool wide_reach = V > 64 && !dense && !large_beam && V <= 2048 && kept_few && !(carried != nullptr && T <= 2);
+    // ones leave no LDS for the survivors by token.  A table spreads the scores, and with 256 threads most lists would
+    // be too long (128 x 500, V = 32, beam 64, R = 0: 2567 us without, 4016 with it), with 512 those of small thresholds
+    // (64 x 150, V = 512, beam 100, R = 0.003: 542 and 610; V = 1024, beam 64, R = 0.001: 617 and 649; V = 128: 847 and
+    // 832).  Beams above 64 leave 256 threads one block of extensions: where every token is kept they stay with 512
+    // threads (32 x 200, V = 32, beam 128: 1344 and 1533; V = 64, beam 100: 1166 and 1488; R = 0.0005, V = 32, beam 100,
+    // which had 256 threads before: 1256 -> 795).  Not for streams of a frame or two
+    // per call.
+    const bool short_calls = carried != nullptr && T <= 2;
+    const bool narrow_reach = !wide && !dense && !short_calls && likely > 8.0 && p.lm_table == nullptr;
+    const bool never_light =
+        short_calls ||
+        (p.rel_threshold == 0.0f && !narrow_reach &&
+         !light_possible(kept_at_most, p.beam, dense && tiny_state ? kThreadsDense : kThreadsSmall, kRegK));
+    const bool wide_reach = V > 64 && !dense && !large_beam && V <= 2048 && kept_few && !short_calls &&
+                            (p.lm_table == nullptr || likely <= 128.0);
     const bool any_reach = narrow_reach || wide_reach;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
