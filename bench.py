@@ -684,7 +684,7 @@ def counter_probe(args, torch, binding, synth, dev):
     r = args.rel_threshold
     out = {"probe": args.counter_probe, "workload": w.name, "rel_threshold": r}
     srcs = ["fltop_prune.hip", "fltop_internal.h"] if args.counter_probe == "prune" else \
-        ["fltop_beam.hip", "fltop_beam_frame.inc", "fltop_beam_light.inc", "fltop_light.h",
+        ["fltop_beam.hip", "fltop_beam_frame.inc", "fltop_beam_light.inc", "fltop_beam_reach.inc", "fltop_light.h",
          "fltop_internal.h"]
     if args.counter_probe == "prune":
         copies = 3
