@@ -65,6 +65,33 @@ def test_masked_tokens_and_gaps_in_the_table(oracle_lib, V, r):
         check(oracle_lib, lp, 40, f"V{V} table{table is not None}", r, lm=table, lm_weight=0.7, insertion_bonus=0.3)
 
 
+def check_beams(oracle_lib, lp, beam, r, top_n=0, **more):
+    """Transcripts, and the whole final beam, of every utterance."""
+    dev = torch.device("cuda:0")
+    B, T, _ = lp.shape
+    ln = np.full(B, T, dtype=np.int32)
+    out = binding.decode(torch.from_numpy(lp).to(dev), torch.from_numpy(ln).to(dev), beam, r, top_n=top_n,
+                         want_nbest=True, **more)
+    got = {k: out[k].cpu().numpy() for k in ("tokens", "lengths", "nbest_count", "nbest_tokens", "nbest_lengths")}
+    want, _, _ = oracle_lib.decode(lp, ln, beam, r, n_threads=8, top_n=top_n)
+    for b in range(B):
+        assert got["tokens"][b, :got["lengths"][b]].tolist() == want[b], b
+        final = oracle_lib.decode_beam(lp[b], beam, r, max_entries=beam, top_n=top_n)
+        mine = [tuple(got["nbest_tokens"][b, i, :got["nbest_lengths"][b, i]]) for i in range(got["nbest_count"][b])]
+        assert sorted(mine) == sorted(tuple(e[0]) for e in final), b
+
+
+@pytest.mark.parametrize("row", [-1e30, float(np.finfo(np.float32).min)])
+@pytest.mark.parametrize("V, beam, r, top_n", [(16, 8, 0.0, 0), (16, 16, 0.0, 0), (20, 40, 0.0, 0), (100, 8, 0.0, 20),
+                                               (100, 70, 0.0, 20)])
+def test_nothing_is_left_out_behind_a_row_of_masked_tokens(oracle_lib, V, beam, r, top_n, row):
+    """All tokens of a frame masked: from there on the scores are so large that what a frame adds is lost, every
+    candidate scores the same and the hashes decide.  The frame itself is one of a run, not its end."""
+    lp = frames(21, 40, 24, V)
+    lp[:, 9] = row
+    check_beams(oracle_lib, lp, beam, r, top_n=top_n)
+
+
 @pytest.mark.parametrize("V, r", [(32, 0.0), (90, 0.002)])
 @pytest.mark.parametrize("cut", [1, 3, 7, 32, 50])
 def test_streams_give_what_the_whole_utterance_gives(V, r, cut):
