@@ -77,6 +77,8 @@ constexpr float kWidestSpread = 1e30f;
 constexpr float light_spread_of(float spread) {
     return __builtin_fminf(__builtin_fmaxf(spread, 0.0f), kWidestSpread);
 }
+// Whether that leaves a spread as it is, with what its rounding adds (NaN: no).
+constexpr bool spread_is_kept(double spread) { return spread < 0.5 * (double)kWidestSpread; }
 
 }  // namespace fltop
 

@@ -92,6 +92,18 @@ def test_nothing_is_left_out_behind_a_row_of_masked_tokens(oracle_lib, V, beam, 
     check_beams(oracle_lib, lp, beam, r, top_n=top_n)
 
 
+@pytest.mark.parametrize("V, beam, r, top_n", [(24, 10, 0.0, 0), (24, 40, 0.0, 0), (31, 16, 0.0, 0), (300, 10, 0.0, 60),
+                                               (300, 40, 0.0, 60)])
+def test_entries_farther_below_than_the_bins_are_wide(oracle_lib, V, beam, r, top_n):
+    """Every token but the blank masked, by sizes from 1e31 to the lowest fp32: a full beam whose worst entry lies
+    farther below the best than any spread that bins are made for, and extensions that come in between."""
+    rng = np.random.default_rng(beam)
+    lp = -10.0 ** rng.uniform(31.0, 38.5, (30, 40, V))
+    lp[:, ::3, 1:] = -10.0 ** rng.uniform(37.5, 38.5, lp[:, ::3, 1:].shape)
+    lp[:, :, 0] = -0.1 - rng.random((30, 40))
+    check_beams(oracle_lib, lp.astype(np.float32), beam, r, top_n=top_n)
+
+
 @pytest.mark.parametrize("V, r", [(32, 0.0), (90, 0.002)])
 @pytest.mark.parametrize("cut", [1, 3, 7, 32, 50])
 def test_streams_give_what_the_whole_utterance_gives(V, r, cut):

@@ -79,3 +79,14 @@ def test_scores_of_every_round_have_a_place(tmp_path, threads):
         CHECK(beam <= stays && s.blocks << s.lg <= behind);
         CHECK({threads} - 1 + (kLightRounds - 1) * behind < light_candidates(beam, {threads}));
     }}""")
+
+
+def test_a_spread_that_is_held_back_is_no_bound(tmp_path):
+    """What `spread_is_kept` says of a spread in fp64, against what becomes of it in fp32."""
+    run(tmp_path, """
+    const double spreads[] = {0.0, 1.0, 1e9, 1e20, 4.9e29, 5.1e29, 1e30, 1e38, 1e39, 1e300, INFINITY, NAN};
+    for (double spread : spreads) {
+        const bool kept = spread_is_kept(spread);
+        if (kept) CHECK((double)light_spread_of((float)spread * 1.0001f + 2e-3f) > spread);
+        CHECK(kept == (spread < 5e29));
+    }""")
