@@ -48,6 +48,9 @@ constexpr int reach_candidates(int beam, int threads, int vocabulary) {
     const int n = s.blocks > 0 ? (reach_list_places(s.blocks, threads, vocabulary) + s.blocks - 1) / s.blocks : 0;
     return stays + n * (threads - stays);
 }
+// Where an entry's last token stands in the table of survivors by token.  The empty prefix has none (-1), and behind the
+// beam's end anything may stand in its place: what LDS, or a stream's record, held before.
+constexpr int light_token_row(bool there, int32_t last) { return there && last > 0 ? last : 0; }
 // Rounds for so many non-blank survivors; more than kLightRounds: not a light frame.
 constexpr int light_rounds(int blocks, int others) {
     int rounds = blocks > 0 ? 1 : kLightRounds + 1;

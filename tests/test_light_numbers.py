@@ -90,3 +90,14 @@ def test_a_spread_that_is_held_back_is_no_bound(tmp_path):
         if (kept) CHECK((double)light_spread_of((float)spread * 1.0001f + 2e-3f) > spread);
         CHECK(kept == (spread < 5e29));
     }""")
+
+
+def test_what_stands_behind_the_beam_is_no_index(tmp_path):
+    """The place of an entry's last token in a table of V + 1: inside, whatever the place of an entry that was
+    never written holds."""
+    run(tmp_path, """
+    const int32_t left_behind[] = {-1, 0, 5, 31, 32, 4096, 1 << 28, 2147483647, -2147483647 - 1};
+    for (int32_t last : left_behind) {
+        CHECK(light_token_row(false, last) == 0);
+        if (last < 32) CHECK(light_token_row(true, last) == (last > 0 ? last : 0));
+    }""")
