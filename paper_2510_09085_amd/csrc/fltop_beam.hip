@@ -180,11 +180,11 @@ struct Generation {
 
 // What the last wavefront says of the next light frame, and of the state that the others do not follow.
 struct alignas(16) LightLine {
-    uint32_t what, live;      // see fltop_beam_light.inc; entries of the beam
+    uint32_t what, live;      // see fltop_beam_reach.inc; entries of the beam
     float lpb, scale;         // log-prob of the blank (-inf: pruned); bins per nat
     double ref, kmax;         // above every candidate's score; above every total
     float spread, margin;
-    int32_t not_light, next_t;
+    int32_t next_t, sure;     // frame that follows; whether the spread is a bound
 };
 
 // What a streaming (chunked) decode carries from one call to the next, per utterance: the
@@ -1232,7 +1232,7 @@ void beam_kernel(BeamArgs a) {
     int light_lg = 0, light_stay_waves = 1, light_blocks = 0;
     const float light_reach = (float)lm_reach + 0.02f;
     float light_spread = 0.0f, light_scale = 0.0f;  // (builds with two wavefronts)
-    int light_not = -1;       // frame that turned out not to be one
+    int light_from = 0, light_misses = 0;  // frame from which on headers are believed; how many in turn did not hold
     const double light_slack = lm_ub + 1.0986122886681098 + 1e-3;
     // whether tokens that cannot reach the beam may be left out: the statistics ask for the number of their
     // pairs with mass, which follows from the tokens unless pairs of the table have none
@@ -1453,7 +1453,7 @@ void beam_kernel(BeamArgs a) {
         }
         if constexpr (kLight) {
             if constexpr (kReach) {
-                if (((light_mask >> l) & 1ull) && t != light_not) {
+                if (((light_mask >> l) & 1ull) && t >= light_from) {
 #include "fltop_beam_reach.inc"
                 }
             } else {

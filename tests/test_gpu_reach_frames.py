@@ -128,3 +128,18 @@ def test_records_that_did_not_fit_are_not_asked_for():
     ln = torch.full((B,), T, dtype=torch.int32, device=dev)
     small = binding.alloc_workspace(B, T, V, beam, dev, max_records=0)
     assert int(binding.decode(lp, ln, beam, 0.0005, workspace=small)["lengths"].min()) == -1
+
+
+def flat(seed, B, T, V, spread):
+    """fp32 [B, T, V] rows without a peak: every token competes in every frame."""
+    x = spread * np.random.default_rng(seed).standard_normal((B, T, V))
+    return (x - np.log(np.exp(x).sum(axis=2, keepdims=True))).astype(np.float32)
+
+
+@pytest.mark.parametrize("V, beam, r", [(16, 64, 0.0), (24, 16, 0.0), (29, 64, 0.001)])
+def test_crowds_at_the_cut_take_a_bounded_time(V, beam, r):
+    """All tokens equal in every frame: hundreds of candidates of one score at the cut.  (Ranked one by one they took 24
+    times as long as candidates whose scores differ; handed to the general path 1.1 to 3 times.)"""
+    from test_gpu_light_frames import fastest_ms
+    equal, apart = (fastest_ms(flat(1, 64, 100, V, spread), beam, r) for spread in (0.0, 0.3))
+    assert equal < 6.0 * apart, (equal, apart)
