@@ -2029,6 +2029,10 @@ static hipError_t compute_units(int* n_cu) {
     return hipSuccess;
 }
 
+// Tokens that a frame of a small vocabulary is expected to keep, above which it goes through those that can reach the
+// beam only: more than fit its header.
+constexpr int kNarrowReachAbove = 8;
+
 hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
                        const fltop_params& p, const Workspace& ws, const StreamSpace* carried,
                        int32_t* out_tokens, int32_t* out_lengths, float* out_scores,
@@ -2068,15 +2072,23 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // "wide" = frames are expected to hold hundreds of candidates or more: a large vocabulary,
     // or a search that is known to keep every token (R = 0) of a small one with a beam to
     // match (measured on V = 32: from 512 candidates per frame on, the 512-thread build is
-    // 9-41% faster; how many tokens a threshold R > 0 keeps is not known here)
+    // 9-41% faster; how many tokens a threshold R > 0 keeps is not known here).  Where frames go through the
+    // tokens that can reach the beam only (see below) and there are more utterances than CUs, two per CU with
+    // 256 threads are faster for fewer candidates, whose blocks of extensions fit those (400 utterances x 60 frames,
+    // R = 0, 512 and 256 threads: V = 16, beam 32 265 and 185 us; V = 32, beam 16 232 and 165; V = 64, beam 32 355
+    // and 343; V = 32, beam 64 394 and 487; V = 64, beam 60 503 and 703; flat emissions, V = 16, beam 64 424 and
+    // 277, V = 64, beam 64 835 and 936).
     const int kept_at_most = p.top_n > 0 && p.top_n < V ? p.top_n : V;
     int n_cu = 0;
     hipError_t qe = compute_units(&n_cu);
     if (qe != hipSuccess) return qe;
     const bool very_dense = (int64_t)B > (int64_t)n_cu * 2;
-    const bool wide =
-        V > 64 || ((very_dense || p.lm_table != nullptr || p.beam > kBeamTiny) && p.rel_threshold == 0.0f &&
-                   (int64_t)p.beam * kept_at_most >= 512);
+    const bool short_calls = carried != nullptr && T <= 2;
+    const bool every_token = V <= 64 && p.rel_threshold == 0.0f;
+    const bool every_reach = every_token && p.lm_table == nullptr && p.beam <= kBeamTiny && !very_dense && !short_calls;
+    const bool two_per_cu = every_reach && B > n_cu && kept_at_most > kNarrowReachAbove;
+    const bool wide = V > 64 || (every_token && (int64_t)p.beam * kept_at_most >= (two_per_cu ? 2048 : 512) &&
+                                 (!two_per_cu || p.beam > 32));
     const bool large_beam = p.beam > kBeamSmall;
     const bool huge_beam = p.beam > kBeamLarge;  // 1024-entry build, 1024 threads, one per CU
     if (huge_beam && (carried != nullptr || V > FLTOP_MAX_VOCAB_WIDE_BEAM))
@@ -2152,26 +2164,30 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // against 75.2; of five 122.5 against 122.7, and beam 8 103.6 against 95.7).
     // Frames that go through the tokens that can reach the beam only (fltop_beam_reach.inc).  Small vocabularies:
     // where frames with competing tokens keep more than the six that fit their header, so that most would
-    // take the general path (64 utterances x 500 frames, V = 32, beam 32, R = 0: 2229 -> 848 us; R = 0.01,
+    // take the general path (64 utterances x 500 frames, V = 32, beam 32, R = 0: 2207 -> 716 us; R = 0.01,
     // where plain light frames do: 384 us against 390, with a table 481 against 535, two utterances fed 25 frames
-    // a call, beam 97, table, window 10: 452 against 557).  Vocabularies above 64 tokens: where frames keep up to 64 (a
-    // lane each), which those that keep every token do not (128 x 400, V = 1024, beam 64, R = 0.01: 769 -> 485 us,
-    // with a table in memory 917 -> 819; R = 0 2721 us without, 2853 with it); the largest
+    // a call, beam 97, table, window 10: 452 against 557).  They have the threads that the general path wants, which
+    // frames that turn out to be none take: with 256 where every token is kept, those of flat emissions took up to
+    // twice as long (64 x 100 frames, V = 64, beam 64, R = 0: 931 us without these frames, 2126 with 256 threads, 1093
+    // with 512; V = 32, beam 16: 407, 584, 309) and the peaked ones no less (batch above: 843).
+    // Vocabularies above 64 tokens: where frames keep up to 64 (a
+    // lane each), which those that keep every token do not (128 x 400, V = 1024, beam 64, R = 0.01: 757 -> 463 us,
+    // with a table in memory 883 -> 803; R = 0 2721 us without, 2853 with it); the largest
     // ones leave no LDS for the survivors by token.  A table spreads the scores, and with 256 threads most lists would
     // be too long (128 x 500, V = 32, beam 64, R = 0: 2567 us without, 4016 with it), with 512 those of small thresholds
     // (64 x 150, V = 512, beam 100, R = 0.003: 542 and 610; V = 1024, beam 64, R = 0.001: 617 and 649; V = 128: 847 and
-    // 832).  Beams above 64 leave 256 threads one block of extensions: where every token is kept they stay with 512
-    // threads (32 x 200, V = 32, beam 128: 1344 and 1533; V = 64, beam 100: 1166 and 1488; R = 0.0005, V = 32, beam 100,
-    // which had 256 threads before: 1256 -> 795).  Not for streams of a frame or two
-    // per call.
-    const bool short_calls = carried != nullptr && T <= 2;
-    const bool narrow_reach = !wide && !dense && !short_calls && likely > 8.0 && p.lm_table == nullptr;
+    // 832).  Small vocabularies that keep every token at beams above 64 have 512 threads without these frames (with 256
+    // they leave one block of extensions: 32 x 200, V = 32, beam 128: 1344 and 1533 us; R = 0.0005, V = 32, beam 100,
+    // which has 256 threads either way: 1256 -> 795).  Not for streams of a frame or two per call (64 streams, V = 64,
+    // beam 64, R = 0, six calls of one frame: 200 us, with 256 threads 334).
+    const bool narrow_reach = !wide && !dense && !short_calls && likely > (double)kNarrowReachAbove && p.lm_table == nullptr;
     const bool never_light =
         short_calls ||
         (p.rel_threshold == 0.0f && !narrow_reach &&
          !light_possible(kept_at_most, p.beam, dense && tiny_state ? kThreadsDense : kThreadsSmall, kRegK));
-    const bool wide_reach = V > 64 && !dense && !large_beam && V <= 2048 && kept_few && !short_calls &&
-                            (p.lm_table == nullptr || likely <= 128.0);
+    const bool wide_reach =
+        V <= 64 ? wide && every_reach
+                : !dense && !large_beam && V <= 2048 && kept_few && !short_calls && (p.lm_table == nullptr || likely <= 128.0);
     const bool any_reach = narrow_reach || wide_reach;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
@@ -2181,7 +2197,7 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     if (!large_beam) {
         const int threads = threads_512 ? kThreadsLarge
                                         : (wide || !dense ? kThreadsSmall : kThreadsDense);
-        a.dcache_rows = dense ? 1 : (wide ? 12 : 8);
+        a.dcache_rows = dense && !wide_reach ? 1 : (wide ? 12 : 8);
         const LightShape shape = light_shape(p.beam, threads);
         // the builds with light frames, whose scores lie there
         const bool plain_light = !wide && !narrow_reach && (tiny_state || !dense);
@@ -2224,14 +2240,14 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
             FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamLarge, 2);
         } else if (wide && very_dense) {
             FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 4, kListsShort);
-        } else if (wide && dense) {
-            FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 4);
         } else if (wide_reach && whole_lists) {
             FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsWhole | kReachFlag);
         } else if (wide_reach && long_lists) {
             FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsLongest | kReachFlag);
         } else if (wide_reach) {
             FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsShort | kReachFlag);
+        } else if (wide && dense) {
+            FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 4);
         } else if (wide) {
             FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 2);
         } else if constexpr (LM == kLmGlobal) {

@@ -32,8 +32,8 @@ constexpr int light_candidates(int beam, int threads) {
 // Frames that go through the tokens that can reach the beam only: how many such tokens at most (a lane holds
 // one), and how many candidates that makes, in up to kReachRounds rounds.  With 256 threads a frame of more than
 // 20 tokens is left to the general path: its candidates crowd about the cut, where they are ranked one by one
-// (64 utterances x 500 frames, V = 32, beam 32, every token kept: 848 us; up to 12 tokens 792, up to 31 1040; 16
-// utterances, beam 42: 941 / 974 / 929 us).  With 512 threads all have a place (128 x 400, V = 1024, beam 64,
+// (64 utterances x 500 frames, V = 32, beam 32, every token kept, which now have 512 threads: 848 us; up to 12 tokens
+// 792, up to 31 1040; 16 utterances, beam 42: 941 / 974 / 929 us).  With 512 threads all have a place (128 x 400, V = 1024, beam 64,
 // table in memory, R = 0.01: 64 tokens 819 us, 20 869, 12 904).
 constexpr int kReachRounds = 8;
 constexpr int reach_list_places(int blocks, int threads, int vocabulary) {
