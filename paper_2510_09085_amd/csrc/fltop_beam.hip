@@ -992,8 +992,8 @@ void beam_kernel(BeamArgs a) {
     static_assert(THREADS >= MB, "one thread per beam entry");
     // builds with 512 threads or more take a thread's candidates from one entry (see EntryView)
     constexpr bool kEntryMajor = THREADS >= kThreadsLarge;
-    // (the floor is made for the entry-major mapping)
-    constexpr bool FLOOR = kEntryMajor && LISTS >= kListsLong;  // with the score floor (see `floored_frame`)
+    static_assert(kEntryMajor || LISTS < kListsLong, "the floor is made for the entry-major mapping");
+    constexpr bool FLOOR = LISTS >= kListsLong;  // with the score floor (see `floored_frame`)
     // ... and a list of the tokens that can reach it
     constexpr bool LISTED = LISTS == kListsLongest;
     static_assert(kEntryMajor || !kColdGlobal, "the largest capacity has no children lists");
@@ -1182,7 +1182,7 @@ void beam_kernel(BeamArgs a) {
     if (has_lm) {
         static_assert(kLmBoundParts == kWave, "one partial maximum per lane");
         const float signed_part = a.lm_bound[lane];
-        if (LISTED || kLight) lm_gaps = __builtin_amdgcn_ballot_w64(__float_as_int(signed_part) < 0) != 0;
+        if (LISTED || kReach) lm_gaps = __builtin_amdgcn_ballot_w64(__float_as_int(signed_part) < 0) != 0;
         float part = fabsf(signed_part);
 #pragma unroll
         for (int o = kWave / 2; o > 0; o >>= 1) part = fmaxf(part, __shfl_xor(part, o, kWave));
@@ -1222,16 +1222,13 @@ void beam_kernel(BeamArgs a) {
     // Light frames: wavefronts [0, light_stay_waves) take the entries that stay; behind them sit
     // light_blocks blocks of 1 << light_lg extensions, one block per non-blank survivor and round.
     int links_are = kLinksBuilt;
-    if constexpr (kLight) {
-        if (tid < 4) sh_left[tid] = 0;
-    }
     const int wave_id = __builtin_amdgcn_readfirstlane(tid / kWave);
     const bool windowed = a.beam_window > 0.0;
     // number of the light frame (above what else stands where the notes are)
     uint32_t light_tag = kReach ? 1u << 24 : 0u;
     int light_lg = 0, light_stay_waves = 1, light_blocks = 0;
     const float light_reach = (float)lm_reach + 0.02f;
-    float light_spread = 0.0f, light_scale = 0.0f;  // (builds with two wavefronts)
+    float light_spread = 0.0f, light_scale = 0.0f;  // (not kReach, whose last wavefront keeps them)
     int light_from = 0, light_misses = 0;  // frame from which on headers are believed; how many in turn did not hold
     const double light_slack = lm_ub + 1.0986122886681098 + 1e-3;
     // whether tokens that cannot reach the beam may be left out: the statistics ask for the number of their
@@ -1327,8 +1324,8 @@ void beam_kernel(BeamArgs a) {
     uint32_t blank_only;  // bit l: blank is the only survivor of frame 32c + l
     int lp_bits;          // lane l: that frame's blank log-prob (fp32 bits), -inf if it was pruned
     uint64_t light_mask = 0;  // bit l: frame 32c + l is a light one ...
-    uint32_t h_desc = 0;      // ... lane l: its survivors (13 bits), whether blank is one (bit 15) and whether
-                              // tokens may be left out (bit 14), blank-only frames behind it (from bit 16)
+    uint32_t h_desc = 0;      // ... lane l: its survivors (13 bits), whether tokens may be left out (bit 14),
+                              // blank-only frames behind it (from bit 16)
     int h_top = 0;            // lane l (fp32 bits): its largest log-prob,
     int h_run = 0;            // no less than the sum of the blank-only frames' behind it (and 2e-3 more at most),
     int h_alone = 0;          // the spread of the beam below which no token reaches it,
@@ -1378,7 +1375,7 @@ void beam_kernel(BeamArgs a) {
             // may not be there)
             const bool light = inside && a.light_off != 0 && others >= 1 && hh.count <= kWave &&
                                (hh.count <= kRegK || hh.rec_base != kNoRecords) && fabsf(frame_best) < INFINITY;
-            h_desc = (uint32_t)(light ? hh.count : 0) | (uint32_t)(tame ? 1 << 14 : 0) | (uint32_t)(with_blank << 15) |
+            h_desc = (uint32_t)(light ? hh.count : 0) | (uint32_t)(tame ? 1 << 14 : 0) |
                      (uint32_t)(run_behind << 16);
             h_top = __float_as_int(frame_best);
             h_rec = hh.rec_base;
@@ -2240,12 +2237,11 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
             FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamLarge, 2);
         } else if (wide && very_dense) {
             FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 4, kListsShort);
-        } else if (wide_reach && whole_lists) {
-            FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsWhole | kReachFlag);
-        } else if (wide_reach && long_lists) {
-            FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsLongest | kReachFlag);
         } else if (wide_reach) {
-            FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsShort | kReachFlag);
+            if constexpr (LM == kLmLds) return hipErrorInvalidValue;  // (a table that small has at most 64 tokens)
+            else if (whole_lists) FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsWhole | kReachFlag);
+            else if (long_lists) FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsLongest | kReachFlag);
+            else FLTOP_LAUNCH_BUILD(kThreadsLarge, kBeamSmall, 2, kListsShort | kReachFlag);
         } else if (wide && dense) {
             FLTOP_LAUNCH_ANY_LISTS(kThreadsLarge, kBeamSmall, 4);
         } else if (wide) {
@@ -2261,7 +2257,8 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
         } else if (never_light) {
             FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsWhole);
         } else if (narrow_reach) {
-            FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsShort | kReachFlag);
+            if constexpr (LM != kLmNone) return hipErrorInvalidValue;  // (calls with a table are none)
+            else FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsShort | kReachFlag);
         } else {
             FLTOP_LAUNCH_BUILD(kThreadsSmall, kBeamSmall, 2, kListsShort);
         }
