@@ -120,6 +120,24 @@ def test_streams_give_what_the_whole_utterance_gives(V, r, cut):
         assert torch.equal(live.tokens[b, :n], want["tokens"][b, :n])
 
 
+@pytest.mark.parametrize("V, r", [(32, 0.0), (29, 0.0005), (90, 0.002)])
+def test_streams_whose_calls_take_different_builds(V, r):
+    """Calls of one or two frames take builds without these frames, the others theirs: what is carried between them
+    holds whichever wrote it."""
+    dev, sizes = torch.device("cuda:0"), [1, 30, 2, 2, 17, 1, 33, 2, 12]
+    T = sum(sizes)
+    lp = torch.from_numpy(frames(13, 3, T, V)).to(dev)
+    want = binding.decode(lp, torch.full((3,), T, dtype=torch.int32, device=dev), 24, r)
+    live, t = binding.Stream(3, T, max(sizes), V, 24, r, dev), 0
+    for n in sizes:
+        live.feed(lp[:, t:t + n].contiguous(), torch.full((3,), n, dtype=torch.int32, device=dev))
+        t += n
+    assert torch.equal(live.lengths, want["lengths"]) and torch.equal(live.scores, want["scores"])
+    for b in range(3):
+        n = int(want["lengths"][b])
+        assert torch.equal(live.tokens[b, :n], want["tokens"][b, :n])
+
+
 def test_records_that_did_not_fit_are_not_asked_for():
     """Survivors of the next full frame are read ahead of its turn: not those of a frame without records."""
     dev = torch.device("cuda:0")
