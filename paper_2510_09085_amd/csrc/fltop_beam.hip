@@ -171,7 +171,7 @@ struct alignas(16) Links {
                                              // entered in this generation's frame, keyed by prefix hash
 };
 
-// One beam generation (both parts of it at one offset from the other generation's).
+// One beam generation.
 template <int MB>
 struct Generation {
     BeamSlab<MB> slab;
@@ -1029,7 +1029,23 @@ void beam_kernel(BeamArgs a) {
 #define FLTOP_USUAL(c) (kEntryMajor ? !!(c) : __builtin_expect(!!(c), 1))
     constexpr int kKidSlots = kEntryMajor ? (kColdGlobal ? 2 * MB : 4 * MB) : 4;
     __shared__ uint32_t kidset2[2][kKidSlots];  // (parent place, token) pairs, per generation
-    __shared__ Generation<MB> gens[2];
+    // The two generations of the beam.  Both parts of one at the same offset from the other's takes fewer registers for
+    // their addresses; the builds for more utterances than CUs are faster with the parts apart (555 utterances x
+    // 100 frames, V = 32, beam 77, R = 0: 2905 us, together 3154; 736 x 38, beam 64, R = 0.007: 122 and 132; the others
+    // together: 64 x 200, V = 73, table, beam 79, R = 0.01 318 us, apart 342; 128 x 400, V = 1024, beam 64, R = 0 2654
+    // and 2704).  (What is not used takes no room.)
+    constexpr bool kTogether = WAVES == 2 || THREADS == kThreadsHuge;
+    __shared__ Generation<MB> both_parts[2];
+    __shared__ BeamSlab<MB> slabs[2];
+    __shared__ Links<MB> all_links[2];
+    auto slab_of = [&](int g) __attribute__((always_inline)) -> BeamSlab<MB>& {
+        if constexpr (kTogether) return both_parts[g].slab;
+        else return slabs[g];
+    };
+    auto links_of = [&](int g) __attribute__((always_inline)) -> Links<MB>& {
+        if constexpr (kTogether) return both_parts[g].links;
+        else return all_links[g];
+    };
     __shared__ __align__(16) uint32_t hfine[kFine];
     __shared__ __align__(16) uint32_t hcoarse[kCoarse];
     __shared__ uint64_t bl_D[kExactCap], bl_h[kExactCap];
@@ -1128,14 +1144,14 @@ void beam_kernel(BeamArgs a) {
         for (int i = tid; i < V * V; i += kThreads) lm_s[i] = a.lm_table[i];
     for (int g2 = 0; g2 < 2; ++g2) {
         if (tid < kMaxBeam) {
-            gens[g2].links.par[tid] = -1;
+            links_of(g2).par[tid] = -1;
             if (!kColdGlobal) {
-                gens[g2].links.first_kid[tid] = -1;
-                gens[g2].links.next_kid[tid] = -1;
+                links_of(g2).first_kid[tid] = -1;
+                links_of(g2).next_kid[tid] = -1;
             }
-            gens[g2].links.kidmask[tid] = 0u;
+            links_of(g2).kidmask[tid] = 0u;
         }
-        for (int i = tid; i < kHashSlots; i += kThreads) gens[g2].links.ht[i] = -1;
+        for (int i = tid; i < kHashSlots; i += kThreads) links_of(g2).ht[i] = -1;
     }
     if (kEntryMajor)
         for (int i = tid; i < 2 * kKidSlots; i += kThreads) (&kidset2[0][0])[i] = kNoKid;
@@ -1162,19 +1178,19 @@ void beam_kernel(BeamArgs a) {
     if (carried) {  // the beam as the previous chunk left it
         __syncthreads();  // the link arrays were just preset by other threads
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&carried->slab);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(&gens[0].slab);
+        uint32_t* dst = reinterpret_cast<uint32_t*>(&slab_of(0));
         for (int i = tid; i < (int)(sizeof(BeamSlab<MB>) / 4); i += kThreads) dst[i] = src[i];
         const uint32_t* lsrc = reinterpret_cast<const uint32_t*>(carried->par);
-        uint32_t* ldst = reinterpret_cast<uint32_t*>(&gens[0].links);
+        uint32_t* ldst = reinterpret_cast<uint32_t*>(&links_of(0));
         for (int i = tid; i < 4 * kMaxBeam; i += kThreads) ldst[i] = lsrc[i];
     } else if (tid == 0) {
-        BeamSlab<MB>& s0 = gens[0].slab;
+        BeamSlab<MB>& s0 = slab_of(0);
         s0.h[0] = kGolden;
         s0.pb[0] = 0.0;
         s0.pnb[0] = -INFINITY;
         s0.ptot[0] = 0.0;
         s0.last[0] = -1;
-        ColdRef<MB>{&gens[0].slab, cold_gen}.set(0, 0, 0, 0, 0);
+        ColdRef<MB>{&slab_of(0), cold_gen}.set(0, 0, 0, 0, 0);
     }
     TrieNode* trie = a.trie + (int64_t)b * trie_stride;
     double lm_ub = 0.0;  // upper bound of any LM term (never below 0)
@@ -1191,8 +1207,8 @@ void beam_kernel(BeamArgs a) {
     const double lm_reach = lm_ub * (1.0 + 0x1p-22);  // the same, whichever way the bound was rounded
     __syncthreads();
     if (kEntryMajor && carried) {  // the pair table is not carried: rebuild it from the links
-        if (tid < carried->n_live && gens[0].links.par[tid] >= 0)
-            kidset_insert(kidset2[0], kKidSlots, gens[0].links.par[tid], gens[0].slab.last[tid]);
+        if (tid < carried->n_live && links_of(0).par[tid] >= 0)
+            kidset_insert(kidset2[0], kKidSlots, links_of(0).par[tid], slab_of(0).last[tid]);
         __syncthreads();
     }
 
@@ -1200,7 +1216,7 @@ void beam_kernel(BeamArgs a) {
     const int floored_above = (kFlooredFrom - 1) * (kThreads / beam);
     int mapped_for = -1;  // kEntryMajor: the beam size the thread -> entry mapping was made for
     int ext_i = 0, ext_g = 0, ext_G = 1;
-    int gen = 0;         // beam generation: gens[gen].slab, gens[gen].links
+    int gen = 0;         // beam generation: slab_of(gen), links_of(gen)
     int n_live = 1;
     bool collapsed = false;  // blank-only frames since the beam was last written
     double kmax_v = 0.0, kmin_v = 0.0;  // bounds of the best / worst score
@@ -1247,15 +1263,15 @@ void beam_kernel(BeamArgs a) {
     }
     // place of an entry's parent in the beam (-1: not there)
     auto parent_place = [&](int j, uint64_t want, int32_t depth) -> int {
-        const int32_t code = gens[gen].links.par[j];
+        const int32_t code = links_of(gen).par[j];
         if (links_are != kLinksCoded) return code;
         if (code >= 0) return newslot[code];
         if (depth == 0 ||
-            ((Tables::of(gens[gen ^ 1].links)[Tables::fresh_word(want)] >> ((uint32_t)want & 31u)) & 1u) == 0)
+            ((Tables::of(links_of(gen ^ 1))[Tables::fresh_word(want)] >> ((uint32_t)want & 31u)) & 1u) == 0)
             return -1;
         int p = -1;
         for (int v = 0; v < n_live; ++v)
-            if (gens[gen].slab.h[v] == want) p = v;
+            if (slab_of(gen).h[v] == want) p = v;
         return p;
     };
     // both generations' tables: empty ones for light frames, empty hash tables for the general path
@@ -1263,16 +1279,16 @@ void beam_kernel(BeamArgs a) {
         constexpr int kHalf = kHashSlots / 4;  // 16 bytes each
         static_assert(!kLight || 2 * kHalf <= kThreads, "one store of a thread");
         if (2 * kHalf == kThreads || tid < 2 * kHalf)
-            reinterpret_cast<int4*>(gens[tid / kHalf].links.ht)[tid % kHalf] = make_int4(v, v, v, v);
+            reinterpret_cast<int4*>(links_of(tid / kHalf).ht)[tid % kHalf] = make_int4(v, v, v, v);
     };
     // parent places and children lists from what a light frame left
     auto build_links = [&](Links<MB>* lk) {
         if (tid < n_live) {
-            const ColdRef<MB> c{&gens[gen].slab, nullptr};
+            const ColdRef<MB> c{&slab_of(gen), nullptr};
             const int p = parent_place(tid, c.hp(tid), c.plen(tid));
             lk->par[tid] = p;
             if (p >= 0) {
-                const int32_t tok = gens[gen].slab.last[tid];
+                const int32_t tok = slab_of(gen).last[tid];
                 if (kEntryMajor) kidset_insert(kidset2[gen], kKidSlots, p, tok);
                 else lk->next_kid[tid] = atomicExch(&lk->first_kid[p], tid);
                 atomicOr(&lk->kidmask[p], 1u << (tok & 31));
@@ -1438,7 +1454,7 @@ void beam_kernel(BeamArgs a) {
         if (FLTOP_RARE(run > 0)) {
             // every entry's total takes the run's log-probs one by one, in frame order, as a
             // plain implementation adds them (the owner thread keeps the sum in a register)
-            BeamSlab<MB>* const cur_run = &gens[gen].slab;
+            BeamSlab<MB>* const cur_run = &slab_of(gen);
             double own = tid < n_live ? cur_run->ptot[tid] : 0.0;
             for (int k = 0; k < run; ++k) {
                 const double x = (double)__int_as_float(__builtin_amdgcn_readlane(lp_bits, l + k));
@@ -1467,8 +1483,8 @@ void beam_kernel(BeamArgs a) {
                     if (links_are == kLinksBuilt) {
                         // the general path came before: its lists go; no parent is among fresh prefixes
                         if (tid < kMaxBeam) {
-                            gens[gen].links.first_kid[tid] = -1;
-                            gens[gen].links.kidmask[tid] = 0u;
+                            links_of(gen).first_kid[tid] = -1;
+                            links_of(gen).kidmask[tid] = 0u;
                             newslot[tid] = tid;
                         }
                         fill_tables(0);
@@ -1481,7 +1497,7 @@ void beam_kernel(BeamArgs a) {
                 }
             }
             if (links_are != kLinksBuilt) {  // the general path looks children up from their parents
-                build_links(&gens[gen].links);
+                build_links(&links_of(gen));
                 lds_barrier();
                 fill_tables(-1);  // its hash tables again (a barrier follows before anything enters them)
             }
@@ -1500,10 +1516,10 @@ void beam_kernel(BeamArgs a) {
         const int K = hd.count;
         const float top = kReach ? frame_top(hd.best, hd.first[0]) : hd.best;
 
-        BeamSlab<MB>* const cur = &gens[gen].slab;
-        BeamSlab<MB>* const nxt = &gens[gen ^ 1].slab;
-        Links<MB>* const lk = &gens[gen].links;
-        Links<MB>* const lkn = &gens[gen ^ 1].links;
+        BeamSlab<MB>* const cur = &slab_of(gen);
+        BeamSlab<MB>* const nxt = &slab_of(gen ^ 1);
+        Links<MB>* const lk = &links_of(gen);
+        Links<MB>* const lkn = &links_of(gen ^ 1);
         const ColdRef<MB> ccur{cur, kColdGlobal ? cold_gen + gen : nullptr};
         const ColdRef<MB> cnxt{nxt, kColdGlobal ? cold_gen + (gen ^ 1) : nullptr};
 
@@ -1775,8 +1791,8 @@ void beam_kernel(BeamArgs a) {
     __syncthreads();
 
     // ---- best prefix (paper: GetHighestScorePrefix) ----------------------------------
-    BeamSlab<MB>& fin = gens[gen].slab;
-    const ColdRef<MB> cfin{&gens[gen].slab, kColdGlobal ? cold_gen + gen : nullptr};
+    BeamSlab<MB>& fin = slab_of(gen);
+    const ColdRef<MB> cfin{&slab_of(gen), kColdGlobal ? cold_gen + gen : nullptr};
     int32_t* wp_node = reinterpret_cast<int32_t*>(hfine);  // the histogram is idle now
     int32_t* wp_depth = wp_node + kWaypoints;
     static_assert(2 * kWaypoints <= kFine, "way-points alias the histogram");
@@ -1921,14 +1937,14 @@ void beam_kernel(BeamArgs a) {
         if constexpr (kLight) {
             if (links_are != kLinksBuilt) {
                 __syncthreads();
-                build_links(&gens[gen].links);
+                build_links(&links_of(gen));
                 __syncthreads();
             }
         }
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(&gens[gen].slab);
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(&slab_of(gen));
         uint32_t* dst = reinterpret_cast<uint32_t*>(&carried->slab);
         for (int i = tid; i < (int)(sizeof(BeamSlab<MB>) / 4); i += kThreads) dst[i] = src[i];
-        const uint32_t* lsrc = reinterpret_cast<const uint32_t*>(&gens[gen].links);
+        const uint32_t* lsrc = reinterpret_cast<const uint32_t*>(&links_of(gen));
         uint32_t* ldst = reinterpret_cast<uint32_t*>(carried->par);
         for (int i = tid; i < 4 * kMaxBeam; i += kThreads) ldst[i] = lsrc[i];
         if (tid == 0) {
