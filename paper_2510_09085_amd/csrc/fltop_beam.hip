@@ -1030,11 +1030,11 @@ void beam_kernel(BeamArgs a) {
     constexpr int kKidSlots = kEntryMajor ? (kColdGlobal ? 2 * MB : 4 * MB) : 4;
     __shared__ uint32_t kidset2[2][kKidSlots];  // (parent place, token) pairs, per generation
     // The two generations of the beam.  Both parts of one at the same offset from the other's takes fewer registers for
-    // their addresses; the builds for more utterances than CUs are faster with the parts apart (555 utterances x
-    // 100 frames, V = 32, beam 77, R = 0: 2905 us, together 3154; 736 x 38, beam 64, R = 0.007: 122 and 132; the others
-    // together: 64 x 200, V = 73, table, beam 79, R = 0.01 318 us, apart 342; 128 x 400, V = 1024, beam 64, R = 0 2654
-    // and 2704).  (What is not used takes no room.)
-    constexpr bool kTogether = WAVES == 2 || THREADS == kThreadsHuge;
+    // their addresses; the builds cut for four wavefronts per SIMD are faster with the parts apart (555 utterances x
+    // 100 frames, V = 32, beam 77, R = 0: 2833 us, together 3154; the others together: 64 x 200, V = 73, table, beam 79,
+    // R = 0.01 318 us, apart 342; 128 x 400, V = 1024, beam 64, R = 0 2654 and 2704; 2527 x 92, beam 20, Top-4, window
+    // 25 599 and 632).  (What is not used takes no room.)
+    constexpr bool kTogether = WAVES < 4 || THREADS == kThreadsHuge;
     __shared__ Generation<MB> both_parts[2];
     __shared__ BeamSlab<MB> slabs[2];
     __shared__ Links<MB> all_links[2];
