@@ -2106,7 +2106,7 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     hipError_t qe = compute_units(&n_cu);
     if (qe != hipSuccess) return qe;
     const bool very_dense = (int64_t)B > (int64_t)n_cu * 2;
-    const bool short_calls = carried != nullptr && T <= 2;
+    const bool short_calls = carried != nullptr && T <= (V <= 64 ? 2 : (p.beam > kBeamTiny ? 8 : 3));
     const bool every_token = V <= 64 && p.rel_threshold == 0.0f;
     const bool every_reach = every_token && p.lm_table == nullptr && p.beam <= kBeamTiny && !very_dense && !short_calls;
     const bool two_per_cu = every_reach && B > n_cu && kept_at_most > kNarrowReachAbove;
@@ -2201,16 +2201,25 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // (64 x 150, V = 512, beam 100, R = 0.003: 542 and 610; V = 1024, beam 64, R = 0.001: 617 and 649; V = 128: 847 and
     // 832).  Small vocabularies that keep every token at beams above 64 have 512 threads without these frames (with 256
     // they leave one block of extensions: 32 x 200, V = 32, beam 128: 1344 and 1533 us; R = 0.0005, V = 32, beam 100,
-    // which has 256 threads either way: 1256 -> 795).  Not for streams of a frame or two per call (64 streams, V = 64,
-    // beam 64, R = 0, six calls of one frame: 200 us, with 256 threads 334).
+    // which has 256 threads either way: 1256 -> 795).  Not for streams of a few frames per call,
+    // which set up for them in vain (64 streams, V = 64, beam 64, R = 0, six calls of one frame: 200 us, with 256 threads
+    // 334; five calls of V = 1024, R = 0.01 without and with them: beam 64, three frames 167 and 178, five 219 and 218;
+    // beam 100, five 284 and 289, eight 320 and 333; V = 73, R = 0.003, beam 98, eight 360 and 356).
     const bool narrow_reach = !wide && !dense && !short_calls && likely > (double)kNarrowReachAbove && p.lm_table == nullptr;
     const bool never_light =
         short_calls ||
         (p.rel_threshold == 0.0f && !narrow_reach &&
          !light_possible(kept_at_most, p.beam, dense && tiny_state ? kThreadsDense : kThreadsSmall, kRegK));
-    const bool wide_reach =
-        V <= 64 ? wide && every_reach
-                : !dense && !large_beam && V <= 2048 && kept_few && !short_calls && (p.lm_table == nullptr || likely <= 128.0);
+    // With a table, one block of extensions (beams above 64) is too little for what large vocabularies list (64 x 200,
+    // V = 972, R = 0.01: beam 64 472 us without, 441 with, beam 79 514 and 562; V = 128, beam 79 457 and 391, but 16
+    // streams of ten frames a call, beam 100 485 and 524), and what a score window asks of every candidate too
+    // much for lists of several rounds (64 x 150, V = 512, R = 0.01, window 10: beam 32 300 and 273, beam 48 326 and
+    // 370; R = 0.1 232 and 205).
+    const bool table_reach =
+        p.lm_table == nullptr ||
+        (likely <= 128.0 && p.beam <= (p.beam_threshold > 0.0 ? (likely > 8.0 ? 32 : kBeamTiny) : (V <= 256 && carried == nullptr ? kBeamSmall : kBeamTiny)));
+    const bool wide_reach = V <= 64 ? wide && every_reach
+                                    : !dense && !large_beam && V <= 2048 && kept_few && !short_calls && table_reach;
     const bool any_reach = narrow_reach || wide_reach;
     // Distance cache: rows for the candidates beyond the one a thread keeps in registers.  A
     // batch that leaves LDS to spare (at most two workgroups per CU) gets 48 KB with 512
