@@ -969,6 +969,53 @@ __device__ __forceinline__ double lane_value(double v, int from) {
     return __longlong_as_double((long long)lane_value((uint64_t)__double_as_longlong(v), from));
 }
 
+// Selection of both kinds of light frames.  Both halves of a word:
+__device__ __forceinline__ uint32_t sum16(uint32_t two, uint32_t acc) {
+    return __builtin_amdgcn_udot2(__builtin_bit_cast(Ushort2, two), Ushort2{1, 1}, acc, false);
+}
+// Counts a candidate in; what its bin held before.  (What is not alive counts into words that nobody reads, one per
+// lane.)
+template <typename Tables>
+__device__ __forceinline__ uint32_t count_in(uint32_t* hist, uint32_t bin, bool live, int lane) {
+    const uint32_t sh = (bin & 1u) * 16u;
+    const int word = live ? (int)(bin >> 1) : Tables::kUnread + lane;
+    return __builtin_amdgcn_ubfe(atomicAdd(&hist[word], 1u << sh), sh, 16u);
+}
+// The row of four bins (row = lane) that a bin lies in; with the candidates before its rows, one per lane, those in better
+// bins than this one, and in this one.
+__device__ __forceinline__ uint64_t row_of(const uint32_t* hist, uint32_t bin) {
+    return reinterpret_cast<const uint64_t*>(hist)[bin >> 2];
+}
+__device__ __forceinline__ int better_than(uint32_t bin, uint64_t row, int before_row, int& same) {
+    const int before = __builtin_amdgcn_ds_bpermute((int)(bin & ~3u), before_row);
+    const uint32_t sh = (bin & 3u) * 16u;
+    const uint64_t lower = row & ~(~0ull << sh);
+    same = (int)((uint32_t)(row >> sh) & 0xFFFFu);
+    return before + (int)sum16((uint32_t)lower, sum16((uint32_t)(lower >> 32), 0u));
+}
+// Place in the new beam, which takes `limit` entries of `most`, of a candidate whose bin fits it (else `most`); `split`: its
+// bin fits only in part.  (What is not alive counts as far behind.)
+__device__ __forceinline__ int place_of(bool live, int ahead, int same, uint32_t number, int limit, int most,
+                                        bool& split) {
+    ahead = live ? ahead : 4 * most;
+    const int end = ahead + same;
+    split = ((ahead - limit) & (limit - end)) < 0;
+    return end <= limit ? ahead + (int)number : most;
+}
+// Score window: only what scores at least the best score less the window is kept.  That is an upper part of the
+// candidates' order like the beam's, so it is enough to know how many.
+__device__ __forceinline__ int kept_by_window(const double* scores, int n, double window, int lane) {
+    uint64_t nearest = kAllOnes;
+    for (int c = lane; c < n; c += kWave) nearest = min(nearest, ~order_key(scores[c]));
+    const double floor = key_value(~wave_min_u64(nearest)) - window;
+    int kept = 0;
+    for (int c = lane; c < n; c += kWave) {
+        const double o = scores[c];
+        kept += __popcll(__builtin_amdgcn_ballot_w64(o >= floor && o > -INFINITY));
+    }
+    return kept;
+}
+
 // State of a beam's parent links between frames: places of the parents, and the children lists that
 // the general path needs; or what a light frame leaves: the parents' places in the beam before, -2
 // for a parent that was not there.
