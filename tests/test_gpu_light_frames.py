@@ -143,8 +143,8 @@ def test_a_table_with_masked_pairs(oracle_lib, mask):
 def test_equal_scores_at_the_cut_few_and_many(beam, tokens, B):
     """Every token of a frame has the same log-prob, so whole generations of candidates tie at the cut, up to 64
     of them (which are listed) and more.  The last bit of a log-sum-exp decides there, so it is compared, bit
-    for bit, with the build that has no light frames (which a vocabulary above 64 tokens takes: the same
-    emissions with tokens that never survive)."""
+    for bit, with a build that has no light frames of either kind (which a vocabulary above 2048 tokens takes: the
+    same emissions with tokens that never survive)."""
     dev = torch.device("cuda:0")
     lp = np.full((3, 150, 12), -30.0, dtype=np.float32)
     lp[:, :, :tokens] = -1.5
@@ -156,7 +156,7 @@ def test_equal_scores_at_the_cut_few_and_many(beam, tokens, B):
         ln[1] = 140
         return binding.decode(torch.from_numpy(np.ascontiguousarray(x)).to(dev), ln, beam, 0.01, **more)
 
-    want = decoded(np.pad(lp, ((0, 0), (0, 0), (0, 60)), constant_values=-60.0), want_nbest=True)
+    want = decoded(np.pad(lp, ((0, 0), (0, 0), (0, 2040)), constant_values=-60.0), want_nbest=True)
     got = decoded(np.tile(lp, (B // 3 + 1, 1, 1))[:B], want_nbest=B == 3)
     for b in range(3):
         if b == 1 and B > 3:

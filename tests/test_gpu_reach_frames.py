@@ -1,8 +1,8 @@
 """Frames that go through the tokens that can reach the beam only: small vocabularies whose frames keep more than
-the six survivors of a header, and vocabularies above 64 tokens (256 and 512 threads).  Against the oracle, statistics
-included: at the beams where the blocks of extensions change size, with lists of one token, of more than one round
-and of more than are taken, with frames that no token changes, masked tokens, gaps in the table, windows, streams
-cut anywhere, and records that did not fit."""
+the six survivors of a header (256 threads where R > 0, 512 where every token is kept), and vocabularies above 64 tokens
+(512).  Against the oracle, statistics included: at the beams where the blocks of extensions change size, with lists of one
+token, of more than one round and of more than are taken, with frames that no token changes, crowds at the cut, masked
+rows and tokens, tables with and without gaps, windows, streams cut anywhere, and records that did not fit."""
 import numpy as np
 import pytest
 import torch
@@ -41,10 +41,26 @@ def check(oracle_lib, lp, beam, label, r, window=0.0, top_n=0, **more):
 @pytest.mark.parametrize("options", ["plain", "window", "lm"])
 @pytest.mark.parametrize("beam", [1, 2, 15, 16, 17, 32, 33, 64, 65, 100, 128])
 def test_small_vocabularies_that_keep_every_token(oracle_lib, beam, options):
+    """(With a table, and at beams above 64, other builds: those without these frames.)"""
     lp = frames(beam, 3, 75, 29)
     lm = synth.make_bigram_lm(29, seed=beam) if options == "lm" else None
     check(oracle_lib, lp, beam, f"beam{beam} {options}", 0.0, window=5.0 if options == "window" else 0.0,
           lm=lm, lm_weight=0.7, insertion_bonus=0.3)
+
+
+@pytest.mark.parametrize("window", [0.0, 5.0])
+@pytest.mark.parametrize("beam", [1, 2, 16, 17, 33, 64, 65, 86, 100, 127, 128])
+def test_small_vocabularies_at_small_thresholds(oracle_lib, beam, window):
+    """256 threads, above beam 64 two wavefronts with the stays and one block of extensions."""
+    check(oracle_lib, frames(50 + beam, 3, 75, 29), beam, f"beam{beam} window{window}", 0.0005, window=window)
+
+
+@pytest.mark.parametrize("beam, V", [(16, 32), (24, 29), (64, 12), (64, 32), (40, 64)])
+def test_more_utterances_than_compute_units_that_keep_every_token(oracle_lib, beam, V):
+    """Two workgroups of 256 threads per CU for few candidates a frame, 512 threads from 2048 on at beams above 32."""
+    B = torch.cuda.get_device_properties(0).multi_processor_count + 5
+    lp = np.tile(frames(60 + beam, 5, 40, V), (B // 5 + 1, 1, 1))[:B]
+    check(oracle_lib, np.ascontiguousarray(lp), beam, f"B{B} beam{beam} V{V}", 0.0)
 
 
 @pytest.mark.parametrize("r, top_n", [(0.01, 0), (0.0005, 0), (0.0, 20), (0.0, 64)])
@@ -52,6 +68,16 @@ def test_small_vocabularies_that_keep_every_token(oracle_lib, beam, options):
                                      (2048, 128)])
 def test_large_vocabularies(oracle_lib, V, beam, r, top_n):
     check(oracle_lib, frames(V + beam, 3, 40, V, zipf=1.1), beam, f"V{V} beam{beam} r{r} N{top_n}", r, top_n=top_n)
+
+
+@pytest.mark.parametrize("window, table", [(4.0, False), (0.0, True), (4.0, True)])
+@pytest.mark.parametrize("V, beam, r", [(65, 30, 0.01), (128, 128, 0.003), (200, 64, 0.01), (1024, 32, 0.01),
+                                        (1024, 64, 0.01)])
+def test_large_vocabularies_with_tables_and_windows(oracle_lib, V, beam, r, window, table):
+    """A table without gaps: tokens are left out, with the statistics asked for."""
+    lm = synth.make_bigram_lm(V, seed=beam) if table else None
+    check(oracle_lib, frames(V + beam + 1, 3, 40, V, zipf=1.1), beam, f"V{V} beam{beam} window{window} table{table}", r,
+          window=window, lm=lm, lm_weight=0.7, insertion_bonus=0.3)
 
 
 @pytest.mark.parametrize("V, r", [(29, 0.0), (70, 0.003)])
@@ -161,6 +187,24 @@ def test_crowds_at_the_cut_take_a_bounded_time(V, beam, r):
     from test_gpu_light_frames import fastest_ms
     equal, apart = (fastest_ms(flat(1, 64, 100, V, spread), beam, r) for spread in (0.0, 0.3))
     assert equal < 6.0 * apart, (equal, apart)
+
+
+@pytest.mark.parametrize("r, beam", [(0.0, 8), (0.0, 24), (0.0, 64), (0.001, 40), (0.001, 128)])
+@pytest.mark.parametrize("step", [0.0, 0.5])
+def test_crowds_at_the_cut_are_ordered_as_the_general_path_does(r, beam, step):
+    """Tokens that are all equal, or in steps: whole generations of candidates tie at the cut, more and fewer than are ranked
+    one by one.  Bit for bit with a build that has no such frames (which a vocabulary above 2048 tokens takes: the same
+    emissions with tokens that have no mass)."""
+    dev = torch.device("cuda:0")
+    lp = flat(beam, 4, 120, 29, 1.0 if step else 0.0)
+    if step:
+        lp = (np.round(lp / step) * step).astype(np.float32)
+    lp[:, 40:70] = frames(beam, 4, 30, 29)
+    ln = torch.full((4,), 120, dtype=torch.int32, device=dev)
+    got, want = (binding.decode(torch.from_numpy(np.ascontiguousarray(x)).to(dev), ln, beam, r, want_nbest=True)
+                 for x in (lp, np.pad(lp, ((0, 0), (0, 0), (0, 2040)), constant_values=-np.inf)))
+    for key in ("tokens", "lengths", "scores", "nbest_count", "nbest_tokens", "nbest_pb", "nbest_pnb"):
+        assert torch.equal(got[key], want[key]), key
 
 
 def test_frames_whose_tokens_all_compete_take_little_longer():

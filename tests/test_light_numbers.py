@@ -101,3 +101,30 @@ def test_what_stands_behind_the_beam_is_no_index(tmp_path):
         CHECK(light_token_row(false, last) == 0);
         if (last < 32) CHECK(light_token_row(true, last) == (last > 0 ? last : 0));
     }""")
+
+
+@pytest.mark.parametrize("threads", [256, 512])
+def test_everything_of_a_listed_token_has_a_place(tmp_path, threads):
+    """Frames that go through a list of tokens: the last thread's last round, and the notes of the list's last token, at
+    the indices the kernel writes them to."""
+    run(tmp_path, f"""
+    const int vocabularies[] = {{2, 5, 21, 29, 64, 65, 300, 2048}};
+    for (int V : vocabularies)
+        for (int beam = 1; beam <= 128; ++beam) {{
+            const LightShape s = light_shape(beam, {threads});
+            const int stays = 64 * s.stay_waves, behind = {threads} - stays;
+            CHECK(s.blocks > 0 && s.blocks << s.lg == behind && beam <= 1 << s.lg);
+            const int places = reach_list_places(s.blocks, {threads}, V);
+            CHECK(places >= 1 && places <= 64 && places < V);  // (a lane each)
+            int last_score = stays - 1, last_note = 0;
+            for (int tid = stays; tid < {threads}; ++tid) {{
+                const int k0 = (tid - stays) >> s.lg, own = (tid - stays) & ((1 << s.lg) - 1);
+                for (int k = k0, slot = tid; k - k0 < places; k += s.blocks, slot += behind) {{
+                    if (slot > last_score) last_score = slot;
+                    const int note = ((k < places ? k : places - 1) << s.lg) + own;
+                    if (note > last_note) last_note = note;
+                }}
+            }}
+            CHECK(last_score < reach_candidates(beam, {threads}, V));
+            CHECK(last_note < places << s.lg);
+        }}""")
