@@ -2234,9 +2234,9 @@ hipError_t launch_beam(const int32_t* lengths, int32_t B, int32_t T, int32_t V,
     // against 75.2; of five 122.5 against 122.7, and beam 8 103.6 against 95.7).
     // Frames that go through the tokens that can reach the beam only (fltop_beam_reach.inc).  Small vocabularies:
     // where frames with competing tokens keep more than the six that fit their header, so that most would
-    // take the general path (64 utterances x 500 frames, V = 32, beam 32, R = 0: 2207 -> 716 us; R = 0.01,
-    // where plain light frames do: 384 us against 390, with a table 481 against 535, two utterances fed 25 frames
-    // a call, beam 97, table, window 10: 452 against 557).  They have the threads that the general path wants, which
+    // take the general path (64 utterances x 500 frames, V = 32, beam 32, R = 0: 2200 -> 705 us; R = 0.01,
+    // where plain light frames do: 384 us against 390 when both came, with a table 481 against 535, two utterances fed
+    // 25 frames a call, beam 97, table, window 10: 452 against 557).  They have the threads that the general path wants, which
     // frames that turn out to be none take: with 256 where every token is kept, those of flat emissions took up to
     // twice as long (64 x 100 frames, V = 64, beam 64, R = 0: 931 us without these frames, 2126 with 256 threads, 1093
     // with 512; V = 32, beam 16: 407, 584, 309) and the peaked ones no less (batch above: 843).
